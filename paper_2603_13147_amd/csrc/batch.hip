@@ -2,15 +2,7 @@
 // 5.8), small SSSP instances, and the batched persistent solve that mixes
 // thousands of them in one launch, with its hipGraph replay and autotuner.
 //
-// Knapsack.  Cell (k, c) of the DP table is forbidden below
-// max(G[k-1][c], v_k + G[k-1][c - w_k]); once row k-1 is final every cell of
-// row k is forbidden exactly until it takes that value, so the workgroup
-// advances a whole row per step.  Thread t keeps cells c = t + i*T (i < CH) of
-// the current row in registers; per item the row is published to LDS, one
-// barrier, and every thread reads the shifted cells c - w_k it needs.  With
-// room for two LDS rows the buffers alternate and one barrier per item
-// suffices; otherwise a second barrier protects the single buffer.  Items
-// heavier than W or worth nothing leave the row unchanged and are skipped.
+// Knapsack.  One workgroup sweeps a DP row per item (knap_rows.h).
 //
 // Small SSSP.  State G[v] = INF - d(v) in LDS (bottom 0, the source INF) and
 // two frontier bitmaps.  Each round every vertex whose bit is set pushes
@@ -32,16 +24,12 @@
 #include <tuple>
 #include <vector>
 
+#include "knap_rows.h"
 #include "llp_dev.h"
 #include "llp_host.h"
 
 namespace llp {
 
-constexpr int KN_MAX_W = 16383;
-
-// Largest workgroup a kernel holding CH row cells per thread in registers is
-// built for (16384 cells per workgroup keeps the register budget).
-constexpr int ch_max_block(int ch) { return 16384 / ch > 1024 ? 1024 : 16384 / ch; }
 constexpr int SS_MAX_N = 8192;
 constexpr size_t BATCH_STATIC_LDS = 64;   // bytes of k_batch's static LDS (claim word, flags), rounded up
 
@@ -54,65 +42,12 @@ struct BCtrl {
     int pad[3];
 };
 
-// --------------------------------------------------------------- knapsack
-// Solve one knapsack instance with the calling workgroup.  buf0 / buf1: LDS
-// rows of W + 1 ints (buf1 == nullptr: single buffer).  Requires
-// CH * blockDim.x >= W + 1.  Returns the status (uniform); the best value is
-// written to *best (thread owning cell W), the last row to row (nullable).
-template <int CH>
-__device__ int knap_wg(const int* wt, const int* val, int items, int W, int* buf0, int* buf1, int* best,
-                       int* row) {
-    const int T = blockDim.x, t = threadIdx.x;
-    int g[CH];
-#pragma unroll
-    for (int i = 0; i < CH; ++i) g[i] = 0;
-    int st = LLP_OK;
-    bool ovf = false;
-    int par = 0;
-    for (int k = 0; k < items; ++k) {
-        const int w = wt[k], v = val[k];
-        if (w < 0 || v < 0) {
-            st = LLP_E_INPUT;
-            break;
-        }
-        if (w > W || v == 0) continue;
-        int* buf = (buf1 && par) ? buf1 : buf0;
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = t + i * T;
-            if (c <= W) buf[c] = g[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = t + i * T;
-            if (c <= W && c >= w) {
-                int y = buf[c - w];
-                if (y > LLP_INF - v) ovf = true;
-                else g[i] = max(g[i], y + v);
-            }
-        }
-        if (!buf1) __syncthreads();
-        par ^= 1;
-    }
-    if (__syncthreads_or(ovf) && st == LLP_OK) st = LLP_E_OVERFLOW;
-#pragma unroll
-    for (int i = 0; i < CH; ++i) {
-        int c = t + i * T;
-        if (c <= W) {
-            if (row) row[c] = g[i];
-            if (c == W && best) *best = g[i];
-        }
-    }
-    return st;
-}
-
 // --------------------------------------------------------------- small SSSP
 // Solve one SSSP instance (out-CSR) with the calling workgroup.  G: LDS
 // int[n]; cur, nxt: LDS bitmaps of ceil(n/32) words; ptr: LDS int[n + 1],
 // filled from gptr; fl: LDS int[4].  dist: output int[n].  Returns the
 // status (uniform).
-__device__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src, int* G,
+__device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src, int* G,
                        unsigned* cur, unsigned* nxt, int* ptr, int* fl, int* dist, int max_rounds,
                        int* rounds_out) {
     const int T = blockDim.x, t = threadIdx.x;
@@ -213,8 +148,8 @@ __device__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, i
 template <int CH>
 __global__ void __launch_bounds__(ch_max_block(CH)) k_knapsack_one(const int* wt, const int* val, int items, int W, int dbuf,
                                                       int* best, int* row, int* status) {
-    extern __shared__ int lds[];
-    int st = knap_wg<CH>(wt, val, items, W, lds, dbuf ? lds + (W + 1) : nullptr, best, row);
+    extern __shared__ unsigned krow[];
+    int st = knap_wg<CH>(wt, val, items, W, krow, dbuf ? krow + (W + 1) : nullptr, best, row);
     if (threadIdx.x == 0) *status = st;
 }
 
@@ -239,17 +174,18 @@ __device__ __forceinline__ bool in_range(long long off, long long len, long long
 }
 
 template <int CH>
-__device__ void batch_one(const BArgs& a, int i, int* lds, int* sfl) {
+__device__ __forceinline__ void batch_one(const BArgs& a, int i, int* lds, int* sfl) {
     const llp_instance d = a.desc[i];
     int st = LLP_OK;
     if (d.kind == LLP_KIND_KNAPSACK) {
         const int items = d.n, W = d.cap_or_source;
-        if (items < 0 || W < 0 || W > a.kn_w || W + 1 > CH * (int)blockDim.x ||
+        if (items < 0 || W < 0 || W > a.kn_w || knap_ch(W, blockDim.x) > CH ||
             !in_range(d.in_off, 2ll * items, a.pool_words) || !in_range(d.out_off, 1, a.out_words)) {
             st = LLP_E_INPUT;
         } else {
             const int* wt = a.pool + d.in_off;
-            st = knap_wg<CH>(wt, wt + items, items, W, lds, a.kn_dbuf ? lds + (a.kn_w + 1) : nullptr,
+            unsigned* row = (unsigned*)lds;
+            st = knap_wg<CH>(wt, wt + items, items, W, row, a.kn_dbuf ? row + (a.kn_w + 1) : nullptr,
                              a.out_pool + d.out_off, nullptr);
         }
     } else if (d.kind == LLP_KIND_SSSP) {
@@ -389,7 +325,7 @@ __global__ void k_batch_limits_reset(BCtrl* c) {
 }
 
 // --------------------------------------------------------------- host
-static const int CH_OPTS[] = {4, 8, 16, 32};
+static const int CH_OPTS[] = {4, 8, 10, 16, 32};
 
 static int pick_ch(int W, int T) {
     for (int ch : CH_OPTS)
@@ -402,6 +338,7 @@ static int dispatch_ch(int ch, F&& f) {
     switch (ch) {
         case 4: return f(std::integral_constant<int, 4>());
         case 8: return f(std::integral_constant<int, 8>());
+        case 10: return f(std::integral_constant<int, 10>());
         case 16: return f(std::integral_constant<int, 16>());
         case 32: return f(std::integral_constant<int, 32>());
         default: return fail(LLP_E_ARG, "no kernel for %d cells per thread", ch);
