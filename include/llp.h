@@ -228,9 +228,13 @@ int llp_solve_jobs(int32_t n, const int32_t* pred_ptr, const int32_t* pred_idx, 
                    const llp_opts* opts);
 
 /* 0-1 knapsack (paper Section 5.8): DP cells G[k][c], k = 0..items,
-   c = 0..W, advanced to max(G[k-1][c], v_k + G[k-1][c - w_k]).  One
+   c = 0..W, advanced to max(G[k-1][c], v_k + G[k-1][c - w_k]).  A
    workgroup sweeps the table a row at a time (every cell of row k is
-   forbidden once row k-1 is final), rows resident in LDS.  wt, val [device]
+   forbidden once row k-1 is final), rows resident in LDS; with many items
+   and a caller's workspace of llp_workspace_bytes(LLP_KIND_KNAPSACK, items,
+   W, opts), the items are split into groups swept by a workgroup each, whose
+   last rows are merged (256 bytes are enough for a solve in one workgroup,
+   which opts->block > 0 also asks for).  wt, val [device]
    int32[items] >= 0; best [device, output] int32[1] = G[items][W];
    last_row [device, output, nullable] int32[W+1] = G[items][.].
    Limits: items >= 0, 0 <= W <= 16383.  Errors: LLP_E_ARG, LLP_E_INPUT

@@ -1,6 +1,6 @@
-// batch.hip - workgroup-local LLP sweeps: the 0-1 knapsack (paper Section
-// 5.8), small SSSP instances, and the batched persistent solve that mixes
-// thousands of them in one launch, with its hipGraph replay and autotuner.
+// batch.hip - workgroup-local LLP sweeps: the batched persistent solve of
+// thousands of 0-1 knapsacks (paper Section 5.8) and small SSSP instances in
+// one launch, with its hipGraph replay and autotuner.
 //
 // Knapsack.  One workgroup sweeps a DP row per item (knap_rows.h).
 //
@@ -145,14 +145,6 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
 }
 
 // --------------------------------------------------------------- kernels
-template <int CH>
-__global__ void __launch_bounds__(ch_max_block(CH)) k_knapsack_one(const int* wt, const int* val, int items, int W, int dbuf,
-                                                      int* best, int* row, int* status) {
-    extern __shared__ unsigned krow[];
-    int st = knap_wg<CH>(wt, val, items, W, krow, dbuf ? krow + (W + 1) : nullptr, best, row);
-    if (threadIdx.x == 0) *status = st;
-}
-
 struct BArgs {
     int count;
     const llp_instance* desc;
@@ -324,97 +316,6 @@ __global__ void k_batch_limits_reset(BCtrl* c) {
     }
 }
 
-// --------------------------------------------------------------- host
-static const int CH_OPTS[] = {4, 8, 10, 16, 32};
-
-static int pick_ch(int W, int T) {
-    for (int ch : CH_OPTS)
-        if ((long long)ch * T >= (long long)W + 1 && T <= ch_max_block(ch)) return ch;
-    return 0;
-}
-
-template <class F>
-static int dispatch_ch(int ch, F&& f) {
-    switch (ch) {
-        case 4: return f(std::integral_constant<int, 4>());
-        case 8: return f(std::integral_constant<int, 8>());
-        case 10: return f(std::integral_constant<int, 10>());
-        case 16: return f(std::integral_constant<int, 16>());
-        case 32: return f(std::integral_constant<int, 32>());
-        default: return fail(LLP_E_ARG, "no kernel for %d cells per thread", ch);
-    }
-}
-
-static size_t lds_limit() {
-    size_t l = device_info().lds_per_block;
-    return l ? l : 65536;
-}
-
-int solve_knapsack(int32_t items, int32_t W, const int32_t* wt, const int32_t* val, int32_t* best,
-                   int32_t* last_row, const llp_opts* opts) {
-    if (items < 0) return fail(LLP_E_ARG, "items must be >= 0 (got %d)", items);
-    if (W < 0 || W > KN_MAX_W) return fail(LLP_E_ARG, "W must be in [0, %d] (got %d)", KN_MAX_W, W);
-    if (!best) return fail(LLP_E_ARG, "best is required");
-    if (items > 0 && (!wt || !val)) return fail(LLP_E_ARG, "wt and val are required");
-    llp_opts o = opts_or_default(opts);
-    hipStream_t st = (hipStream_t)o.stream;
-    int T = o.block > 0 ? o.block : 1024;
-    if (T % 64 != 0 || T > 1024) return fail(LLP_E_ARG, "block must be a multiple of 64 up to 1024");
-    const int ch = pick_ch(W, T);
-    if (!ch) return fail(LLP_E_ARG, "W = %d needs more than 32 cells per thread at %d threads", W, T);
-    const size_t row_bytes = (size_t)(W + 1) * 4;
-    const int dbuf = 2 * row_bytes <= lds_limit();
-    const size_t lds = dbuf ? 2 * row_bytes : row_bytes;
-    if (lds > lds_limit()) return fail(LLP_E_ARG, "a row of W = %d does not fit in LDS", W);
-    size_t need = 256;
-    void* ws = nullptr;
-    int s = get_workspace(o, need, &ws);
-    if (s) return s;
-    int* status = (int*)ws;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    const bool timing = (o.flags & LLP_TIMING) && o.stats;
-    if (timing) {
-        LLP_HIP(hipEventCreate(&ev0));
-        LLP_HIP(hipEventCreate(&ev1));
-        LLP_HIP(hipEventRecord(ev0, st));
-    }
-    s = dispatch_ch(ch, [&](auto c) {
-        constexpr int CH = decltype(c)::value;
-        if (lds > 65536) (void)hipFuncSetAttribute((const void*)k_knapsack_one<CH>,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_knapsack_one<CH>, dim3(1), dim3(T), lds, st, wt, val, items, W, dbuf, best,
-                           last_row, status);
-        return hip_check(hipGetLastError(), "k_knapsack_one");
-    });
-    if (s) return s;
-    if (timing) LLP_HIP(hipEventRecord(ev1, st));
-    if (o.flags & LLP_ASYNC) {
-        if (o.status_dev) LLP_HIP(hipMemcpyAsync(o.status_dev, status, 4, hipMemcpyDeviceToDevice, st));
-        return LLP_OK;
-    }
-    int h = 0;
-    s = readback(st, status, &h, sizeof(h));
-    if (s) return s;
-    if (o.stats) {
-        memset(o.stats, 0, sizeof(*o.stats));
-        o.stats->rounds = items;
-        o.stats->advances = (int64_t)items * (W + 1);
-        if (timing) {
-            float ms = 0.f;
-            LLP_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-            o.stats->device_ms = ms;
-        }
-    }
-    if (timing) {
-        (void)hipEventDestroy(ev0);
-        (void)hipEventDestroy(ev1);
-    }
-    if (h == LLP_E_INPUT) return fail(h, "negative weight or value");
-    if (h == LLP_E_OVERFLOW) return fail(h, "a DP value does not fit int32");
-    if (h) return fail(h, "device status %d", h);
-    return LLP_OK;
-}
-
 // ---------------------------------------------------------------- batch
 static std::mutex g_bmu;
 
@@ -478,7 +379,7 @@ static int batch_plan(int32_t count, const llp_instance* desc, const llp_opts& o
     size_t need1 = row > ss ? row : ss;
     size_t need2 = 2 * row > ss ? 2 * row : ss;
     // k_batch's own LDS (the claim word and the solver flags) comes first
-    const size_t lim = lds_limit() - BATCH_STATIC_LDS;
+    const size_t lim = lds_per_workgroup() - BATCH_STATIC_LDS;
     p->kn_dbuf = need2 <= lim;
     p->lds = p->kn_dbuf ? need2 : need1;
     if (p->lds > lim) return fail(LLP_E_ARG, "instances need %zu bytes of LDS", p->lds);
@@ -823,11 +724,6 @@ int autotune_get(int kind, int32_t* block, int32_t* chunk) {
 }  // namespace llp
 
 extern "C" {
-
-int llp_solve_knapsack(int32_t items, int32_t W, const int32_t* wt, const int32_t* val, int32_t* best,
-                       int32_t* last_row, const llp_opts* opts) {
-    return llp::solve_knapsack(items, W, wt, val, best, last_row, opts);
-}
 
 int llp_solve_batch(int32_t count, const llp_instance* desc, const int32_t* pool, int64_t pool_words,
                     int32_t* out_pool, int64_t out_words, int32_t* out_status, const llp_opts* opts) {

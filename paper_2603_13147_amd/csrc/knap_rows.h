@@ -29,8 +29,8 @@
 
 #include <utility>
 
-#include "../../include/llp.h"
 #include "llp_dev.h"
+#include "llp_host.h"
 
 namespace llp {
 
@@ -156,6 +156,33 @@ __device__ __forceinline__ int knap_wg(const int* wt, const int* val, int items,
         }
     });
     return __syncthreads_or(over) && st == LLP_OK ? LLP_E_OVERFLOW : st;
+}
+
+// --------------------------------------------------------------- host
+// Kernels are compiled for these largest counts of cells per thread.
+static const int CH_OPTS[] = {4, 8, 10, 16, 32};
+
+static int pick_ch(int W, int T) {
+    for (int ch : CH_OPTS)
+        if ((long long)ch * T >= (long long)W + 1 && T <= ch_max_block(ch)) return ch;
+    return 0;
+}
+
+template <class F>
+static int dispatch_ch(int ch, F&& f) {
+    switch (ch) {
+        case 4: return f(std::integral_constant<int, 4>());
+        case 8: return f(std::integral_constant<int, 8>());
+        case 10: return f(std::integral_constant<int, 10>());
+        case 16: return f(std::integral_constant<int, 16>());
+        case 32: return f(std::integral_constant<int, 32>());
+        default: return fail(LLP_E_ARG, "no kernel for %d cells per thread", ch);
+    }
+}
+
+static inline size_t lds_per_workgroup() {
+    const size_t l = device_info().lds_per_block;
+    return l ? l : 65536;
 }
 
 }  // namespace llp

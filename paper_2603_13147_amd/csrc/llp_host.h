@@ -70,6 +70,37 @@ int get_workspace(const llp_opts& o, size_t bytes, void** out);
 // Small pinned host buffer per thread and device, for status readback.
 void* pinned_scratch(size_t bytes);
 
+// Workspace of a knapsack (knapsack.hip): a header, then the rows of the groups
+// the items are split into and of their merges (2 KN_GROUPS rows at most).
+// A workspace of the header alone is enough for a solve that is not split.
+constexpr size_t KN_HEADER_BYTES = 256;
+constexpr int KN_GROUPS = 32;
+inline size_t knap_stride(int64_t W) { return ((size_t)W + 4) & ~(size_t)3; }   // words per row
+
+// Groups (a power of two) the items of one knapsack are split into: the count
+// whose estimated time is least.  Measured on an MI355X, in ns: 290 +
+// 0.026 W per item of a group's row sweep, 9000 per level of merges (launch
+// and latency) and 4000 for the finishing launch, 5.6e-5 W^2 per merge.  So 64
+// items at W = 256 stay whole (33 us, 36 as two groups), 256 at W = 4000 take
+// 8 groups (65 us, 115 whole), 4000 at W = 6400 take 32 (195 us, 2049 whole)
+// and 4000 at W = 16383 take 16 (455 us, 2736 whole, 599 as 32).
+inline int knap_groups(int64_t items, int64_t W) {
+    int best = 1;
+    int64_t best_ns = INT64_MAX;
+    for (int k = 0; (1 << k) <= KN_GROUPS; ++k) {
+        const int64_t ns = (items >> k) * (290 + W * 26 / 1000) + (k ? 4000 + 9000 * k : 0) +
+                           ((1 << k) - 1) * (W * W / 17857);
+        if (ns < best_ns) {
+            best_ns = ns;
+            best = 1 << k;
+        }
+    }
+    return best;
+}
+inline size_t knap_bytes(int groups, int64_t W) {
+    return KN_HEADER_BYTES + (groups > 1 ? (size_t)2 * groups * knap_stride(W) * 4 : 0);
+}
+
 // Wait for the stream and read `bytes` from device pointer src into dst via the
 // pinned scratch buffer.
 int readback(hipStream_t s, const void* src, void* dst, size_t bytes);

@@ -1,7 +1,9 @@
 """GPU parity of the knapsack row sweep at the edges of its layout: cells per
 thread just full and just over, rows that end inside a wave, weights at a
 wave's first and last cell, item counts around the 64 loaded at a time, and
-values around 2^31 - 1."""
+values around 2^31 - 1; and of the split into groups of items whose rows are
+merged, against the oracle and against the same solve in a workspace too
+small for the split."""
 import numpy as np
 import pytest
 
@@ -51,4 +53,40 @@ def test_knapsack_values_at_the_int32_bound(k):
     wt[k - 1] = -1
     with pytest.raises(llp.LLPError) as e:
         llp.knapsack(wt, val, k)
+    assert e.value.status == llp.E_INPUT
+
+
+@pytest.mark.parametrize("items,W", [(33, 40), (100, 255), (257, 511), (257, 512), (300, 513), (1000, 767),
+                                     (1000, 1024), (401, 4097), (999, 16383)])
+def test_knapsack_split(items, W):
+    wt, val = items_of(W, items, seed=77 + W)
+    want, want_row = oracle.knapsack(wt, val, W, row=True)
+    for ws in (None, torch.empty(256, dtype=torch.uint8, device="cuda")):
+        best, row = llp.knapsack(wt, val, W, row=True, ws=ws)
+        assert best == want
+        assert np.array_equal(row.cpu().numpy(), want_row)
+
+
+def test_knapsack_split_reused_workspace_and_errors():
+    """Solves of other sizes in one workspace leave nothing behind; a bad item
+    in the last group and an overflow that only the merges reach are seen."""
+    W, k = 1500, 2000
+    ws = llp.workspace(llp.KIND_KNAPSACK, 4000, 6400)
+    for seed, (n, cap) in enumerate([(k, W), (4000, 6400), (700, 300), (k, W)]):
+        wt, val = items_of(cap, n, seed=seed)
+        best, row = llp.knapsack(wt, val, cap, row=True, ws=ws)
+        want, want_row = oracle.knapsack(wt, val, cap, row=True)
+        assert best == want and np.array_equal(row.cpu().numpy(), want_row)
+    ones = np.ones(W, np.int32)
+    val = np.full(W, (2**31 - 1) // W, np.int32)
+    val[7] += (2**31 - 1) - int(val.astype(np.int64).sum())
+    assert llp.knapsack(ones, val, W, ws=ws) == 2**31 - 1
+    val[W - 1] += 1
+    with pytest.raises(llp.LLPError) as e:
+        llp.knapsack(ones, val, W, ws=ws)
+    assert e.value.status == llp.E_OVERFLOW
+    bad = ones.copy()
+    bad[W - 1] = -1
+    with pytest.raises(llp.LLPError) as e:
+        llp.knapsack(bad, val, W, ws=ws)
     assert e.value.status == llp.E_INPUT
