@@ -226,14 +226,17 @@ __global__ void k_sm_chain(SArgs a, int r) {
     if (lane() == 0 && tot) atomicAdd((unsigned long long*)&c->proposals, (unsigned long long)tot);
 }
 
-// One workgroup runs every chain of a cold start with n <= SM_LDS_MAX:
-// best[] and the proposal indices live in LDS, so the displacement atomic and
-// the look-ahead's best-key reads stay on the CU (a chain's steps are
-// dependent; across XCDs an atomic must reach the memory side).  Thread t
-// starts men t, t + 1024, ... in turn and carries displaced men as above.
-constexpr int SM_LDS_MAX = 12288;   // 12 B of LDS per man: 144 KB
+// One workgroup runs every chain of a cold start with n <= SM_LDS_MAX: the
+// women's best keys and the men's positions live in LDS, so the displacement
+// atomic and the reads of the keys stay on the CU (across XCDs an atomic must
+// reach the memory side).  See k_sm_lds.
+constexpr int SM_LDS_MAX = 12288;   // 8 B of LDS per man: 96 KB
 constexpr int SM_COMBO = 64;        // list positions per man held as (woman, rank) pairs
-constexpr int SM_LDS_LOOKAHEAD = 6;   // women examined per round trip of a chain in k_sm_lds
+constexpr int SM_LDS_LOOKAHEAD = 6;   // women examined per round trip of a thread's chain in k_sm_lds
+constexpr unsigned SM_FREE = ~0u;   // key of a woman nobody holds
+constexpr int SM_MAN_BITS = 14;     // a key is rank << 14 | man (n <= SM_LDS_MAX < 2^14)
+constexpr int SM_MAN = (1 << SM_MAN_BITS) - 1;
+constexpr int SM_HOPS = 16;         // steps of a thread's chain before its man is parked
 constexpr int SM_LDS_THREADS = 1024;
 
 // The i-th woman w on m's list and her rank of m, as w | rank << 16.
@@ -257,81 +260,156 @@ __global__ void k_sm_combo(SArgs a) {
     a.combo[(long long)m * SM_COMBO + i] = sm_pair(a, m, i);
 }
 
+// A chain step takes the man displaced last, finds the first woman on the
+// rest of his list whose key his own beats, and displaces her holder.  It is
+// bound by latency: a row of the table from the L2, the women's keys from
+// LDS, and the next man is known.  Two forms:
+//  - a thread per chain, 6 women per step, while there is a chain for every
+//    thread: up to SM_HOPS steps per man, then the man of the moment is parked;
+//  - a wave per chain for the parked men (the chains that are left are few
+//    and long): a lane per list position, so a man's whole row of 64 is one
+//    load and a ballot finds his woman, however many reject him.  Her holder
+//    is in the key read, so his row is loaded before the atomicMin that
+//    displaces him returns; if another chain came between, the row is dropped.
+// A man's position nx (the next one to try) is written before the atomicMin
+// that places him (LDS operations of a wave stay in order), so whoever reads
+// his key reads his position too.
+// Whole solves, three random markets each: n = 8192 522-1202 us (4.55-5.49 ms
+// with a thread per chain throughout), n = 3000 203-294, n = 1000 155-207 us.
+// Without the first form 962-1626 us at n = 8192, with 4 or 64 steps in it
+// 589-1261 and 517-1192; without touching the table first 572-1341.
 __global__ void __launch_bounds__(SM_LDS_THREADS) k_sm_lds(SArgs a) {
-    __shared__ unsigned long long best[SM_LDS_MAX];
-    __shared__ int gl[SM_LDS_MAX];
+    __shared__ unsigned best[SM_LDS_MAX];
+    __shared__ unsigned short nx[SM_LDS_MAX];
+    __shared__ unsigned short pend[SM_LDS_MAX];
+    __shared__ int npend, head, bad;
     SCtrl* c = a.ctrl;
-    const int n = a.n;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        best[i] = SM_EMPTY;
-        gl[i] = 0;
+    const int n = a.n, k = min(n, SM_COMBO), l = lane();
+    for (int i = threadIdx.x; i < n; i += SM_LDS_THREADS) {
+        best[i] = SM_FREE;
+        nx[i] = 0;
     }
+    if (threadIdx.x == 0) npend = head = bad = 0;
+    // one word of every line of the table, so that a chain's first visit to a
+    // row finds it in this XCD's L2 (the table was written from all of them)
+    int x = 0;
+    for (int i = threadIdx.x * 32; i < n * SM_COMBO; i += SM_LDS_THREADS * 32) x |= a.combo[i];
+    asm volatile("" ::"v"(x));
     __syncthreads();
-    long long made = 0;
-    bool infeasible = false;
-    for (int t = threadIdx.x; t < n && !infeasible; t += blockDim.x) {
+    for (int t = threadIdx.x; t < n; t += SM_LDS_THREADS) {
         int m = t, g = 0;
-        for (;;) {
-            if (g >= n) {
-                infeasible = true;
+        bool park = true;
+        for (int hop = 0; hop < SM_HOPS && g < k; ++hop) {
+            // positions past the table's end read its last entry, whose woman
+            // is then taken only at her own position
+            int cw[SM_LDS_LOOKAHEAD];
+            unsigned bv[SM_LDS_LOOKAHEAD];
+#pragma unroll
+            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) cw[i] = a.combo[m * SM_COMBO + min(g + i, k - 1)];
+#pragma unroll
+            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) bv[i] = best[cw[i] & 0xffff];
+            int at = -1, w = 0;
+            unsigned key = 0;
+#pragma unroll
+            for (int i = SM_LDS_LOOKAHEAD - 1; i >= 0; --i) {
+                const unsigned ki = ((unsigned)cw[i] >> 16 << SM_MAN_BITS) | (unsigned)m;
+                if (g + i < k && ki < bv[i]) {
+                    at = g + i;
+                    w = cw[i] & 0xffff;
+                    key = ki;
+                }
+            }
+            if (at < 0) {
+                g = min(g + SM_LDS_LOOKAHEAD, k);
+                continue;
+            }
+            nx[m] = (unsigned short)(at + 1);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            const unsigned old = atomicMin(&best[w], key);
+            if (old == SM_FREE) {
+                park = false;
                 break;
             }
-            const int la = min(SM_LDS_LOOKAHEAD, n - g);
-            int wv[SM_LDS_LOOKAHEAD], cw[SM_LDS_LOOKAHEAD];
-            unsigned long long kv[SM_LDS_LOOKAHEAD], bv[SM_LDS_LOOKAHEAD];
-            if (g + SM_LDS_LOOKAHEAD <= SM_COMBO) {   // the whole look-ahead window is in the table
-#pragma unroll
-                for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) cw[i] = i < la ? a.combo[(long long)m * SM_COMBO + g + i] : 0;
+            if (old > key) {
+                m = (int)(old & SM_MAN);
+                g = nx[m];
             } else {
-#pragma unroll
-                for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i)
-                    cw[i] = i >= la ? 0 : g + i < SM_COMBO ? a.combo[(long long)m * SM_COMBO + g + i] : sm_pair(a, m, g + i);
+                g = at + 1;
             }
-#pragma unroll
-            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) {
-                wv[i] = cw[i] & 0xffff;   // < n: sm_pair guarded it
-                kv[i] = ~0ull;
-                bv[i] = 0ull;
-                if (i < la) {
-                    kv[i] = sm_key(cw[i] >> 16, m, g + i);
-                    bv[i] = best[wv[i]];
-                }
-            }
-            int skip = 0;
-#pragma unroll
-            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i)
-                if (skip == i && i < la && bv[i] < kv[i]) skip = i + 1;
-            if (skip == la) {
-                g += la;
-                made += la;
-                continue;
-            }
-            g += skip;
-            made += skip + 1;
-            int w = 0;
-            unsigned long long key = 0;
-#pragma unroll
-            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i)
-                if (i == skip) {
-                    w = wv[i];
-                    key = kv[i];
-                }
-            const unsigned long long old = atomicMin(&best[w], key);
-            if (old < key) {
-                ++g;
-                continue;
-            }
-            atomicMax(&gl[m], g);
-            if (old == SM_EMPTY || old == key) break;
-            m = guard((int)((old >> 16) & 0xffffull), n, c->diag, 3, w, (int)(old & 0xffff));
-            g = (int)(old & 0xffffull) + 1;
+        }
+        if (park) {
+            nx[m] = (unsigned short)g;
+            pend[atomicAdd(&npend, 1)] = (unsigned short)m;
         }
     }
-    if (infeasible) set_status(&c->status, LLP_E_INFEASIBLE);
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) a.G[i] = gl[i];
+    const int np = npend;
+    for (;;) {
+        int q = 0;
+        if (l == 0) q = atomicAdd(&head, 1);
+        q = __builtin_amdgcn_readfirstlane(q);
+        if (q >= np) break;
+        int m = __builtin_amdgcn_readfirstlane((int)pend[q]);
+        int row = l < k ? a.combo[m * SM_COMBO + l] : 0;
+        int g = __builtin_amdgcn_readfirstlane((int)nx[m]);
+        for (;;) {
+            // the first of m's women from position g on who prefers him
+            int at = -1, w = row & 0xffff;
+            unsigned key = ((unsigned)row >> 16 << SM_MAN_BITS) | (unsigned)m;
+            unsigned bv = l >= g && l < k ? best[w] : 0u;
+            uint64_t ok = ballot(key < bv);
+            for (int b = max(g, k); !ok && b < n; b += LLP_WAVE) {   // past the table: the list and the rank
+                const int p = b + l < n ? sm_pair(a, m, b + l) : 0;
+                w = p & 0xffff;
+                key = ((unsigned)p >> 16 << SM_MAN_BITS) | (unsigned)m;
+                bv = b + l < n ? best[w] : 0u;
+                ok = ballot(key < bv);
+                at = b;
+            }
+            if (!ok) {
+                if (l == 0) bad = 1;   // he exhausted his list
+                break;
+            }
+            const int i = __ffsll((long long)ok) - 1;
+            at = max(at, 0) + i;
+            const int wi = __builtin_amdgcn_readlane(w, i);
+            const unsigned ki = (unsigned)__builtin_amdgcn_readlane((int)key, i);
+            const unsigned seen = (unsigned)__builtin_amdgcn_readlane((int)bv, i);
+            // her holder's row and position, on the way while he is displaced
+            const int m2 = seen == SM_FREE ? m : (int)(seen & SM_MAN);
+            const int row2 = l < k ? a.combo[m2 * SM_COMBO + l] : 0;
+            const int g2 = nx[m2];
+            unsigned old = 0;
+            if (l == 0) {
+                nx[m] = (unsigned short)(at + 1);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                old = atomicMin(&best[wi], ki);
+            }
+            old = (unsigned)__builtin_amdgcn_readfirstlane((int)old);
+            if (old == SM_FREE) break;
+            if (old == seen) {
+                m = m2;
+                row = row2;
+                g = __builtin_amdgcn_readfirstlane(g2);
+            } else if (old < ki) {   // another chain was first: m tries on
+                g = at + 1;
+            } else {                 // another chain's man is displaced instead
+                m = (int)(old & SM_MAN);
+                row = l < k ? a.combo[m * SM_COMBO + l] : 0;
+                g = __builtin_amdgcn_readfirstlane((int)nx[m]);
+            }
+        }
+    }
+    __syncthreads();
+    if (bad && threadIdx.x == 0) set_status(&c->status, LLP_E_INFEASIBLE);
+    // a man's proposals are the positions he tried
+    long long made = 0;
+    for (int i = threadIdx.x; i < n; i += SM_LDS_THREADS) {
+        a.G[i] = max((int)nx[i] - 1, 0);
+        made += nx[i];
+    }
     const long long tot = wave_sum64(made);
-    if (lane() == 0 && tot) atomicAdd((unsigned long long*)&c->proposals, (unsigned long long)tot);
+    if (l == 0 && tot) atomicAdd((unsigned long long*)&c->proposals, (unsigned long long)tot);
     if (threadIdx.x == 0) {
         c->done = 1;
         c->last_round = 1;
