@@ -4,12 +4,7 @@
 //
 // Knapsack.  One workgroup sweeps a DP row per item (knap_rows.h).
 //
-// Small SSSP.  State G[v] = INF - d(v) in LDS (bottom 0, the source INF) and
-// two frontier bitmaps.  Each round every vertex whose bit is set pushes
-// single-arc partial advances G[x] <- max(G[x], G[u] - w) along its out-arcs
-// with LDS atomicMax (Definition 3: a partial maximum is an alpha-forbidden
-// advance), marking the advanced vertices for the next round, until a round
-// advances nothing.
+// Small SSSP.  One workgroup, the state in LDS (sssp_wg.h).
 //
 // Batch.  A persistent grid; each workgroup claims `chunk` consecutive
 // instances from a device queue counter and solves them one after another.
@@ -25,13 +20,14 @@
 #include <vector>
 
 #include "knap_rows.h"
+#include "sssp_wg.h"
 #include "llp_dev.h"
 #include "llp_host.h"
 
 namespace llp {
 
 constexpr int SS_MAX_N = 8192;
-constexpr size_t BATCH_STATIC_LDS = 64;   // bytes of k_batch's static LDS (claim word, flags), rounded up
+constexpr size_t BATCH_STATIC_LDS = 320;   // bytes of k_batch's static LDS (claim word, flags), rounded up
 
 struct BCtrl {
     int head;          // queue: next unclaimed instance
@@ -41,108 +37,6 @@ struct BCtrl {
     int bad_kind;
     int pad[3];
 };
-
-// --------------------------------------------------------------- small SSSP
-// Solve one SSSP instance (out-CSR) with the calling workgroup.  G: LDS
-// int[n]; cur, nxt: LDS bitmaps of ceil(n/32) words; ptr: LDS int[n + 1],
-// filled from gptr; fl: LDS int[4].  dist: output int[n].  Returns the
-// status (uniform).
-__device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src, int* G,
-                       unsigned* cur, unsigned* nxt, int* ptr, int* fl, int* dist, int max_rounds,
-                       int* rounds_out) {
-    const int T = blockDim.x, t = threadIdx.x;
-    const int words = (n + 31) >> 5;
-    for (int v = t; v < n; v += T) G[v] = (v == src) ? LLP_INF : 0;
-    for (int v = t; v <= n; v += T) ptr[v] = gptr[v];   // row offsets held in LDS for every round
-    for (int i = t; i < words; i += T) {
-        cur[i] = (i == (src >> 5)) ? (1u << (src & 31)) : 0u;
-        nxt[i] = 0u;
-    }
-    if (t < 4) fl[t] = 0;   // fl[0], fl[1]: advanced in round parity; fl[2]: bad input; fl[3]: overflow
-    __syncthreads();
-    int r = 0;
-    for (;; ++r) {
-        if (r >= max_rounds) break;
-        bool adv = false, bad = false, ovf = false;
-        for (int u = t; u < n; u += T) {
-            if (!(cur[u >> 5] & (1u << (u & 31)))) continue;
-            int b = ptr[u], e = ptr[u + 1];
-            if (b < 0 || e > m || e < b) {
-                bad = true;
-                continue;
-            }
-            const int gu = G[u];
-            for (int k0 = b; k0 < e; k0 += 8) {
-                // the arcs' loads are all issued before any is checked
-                int xs[8], ws[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = k0 + j < e ? k0 + j : b;
-                    xs[j] = dst[k];
-                    ws[j] = wgt[k];
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    if (k0 + j >= e) break;
-                    const int x = xs[j], w = ws[j];
-                    if ((unsigned)x >= (unsigned)n || w < 0) {
-                        bad = true;
-                        continue;
-                    }
-                    int cand = gu - w;
-                    if (cand <= 0) {
-                        ovf = true;
-                        continue;
-                    }
-                    if (cand > G[x]) {
-                        int old = atomicMax(&G[x], cand);
-                        if (old < cand) {
-                            atomicOr(&nxt[x >> 5], 1u << (x & 31));
-                            adv = true;
-                        }
-                    }
-                }
-            }
-        }
-        if (adv) fl[r & 1] = 1;
-        if (bad) fl[2] = 1;
-        if (ovf) fl[3] = 1;
-        __syncthreads();
-        const bool more = fl[r & 1] != 0 && fl[2] == 0;
-        // clear the bitmap the next round fills and the next round's flag
-        for (int i = t; i < words; i += T) cur[i] = 0u;
-        if (t == 0) fl[(r + 1) & 1] = 0;
-        __syncthreads();
-        unsigned* tmp = cur;
-        cur = nxt;
-        nxt = tmp;
-        if (!more) {
-            ++r;
-            break;
-        }
-    }
-    int st = LLP_OK;
-    if (fl[2]) st = LLP_E_INPUT;
-    else if (r >= max_rounds && fl[(r - 1) & 1]) st = LLP_E_NOT_CONVERGED;
-    // overflow: an unreached vertex with a reached in-neighbour
-    if (st == LLP_OK && fl[3]) {
-        bool o = false;
-        for (int u = t; u < n; u += T) {
-            if (G[u] <= 0) continue;
-            for (int k = max(ptr[u], 0); k < min(ptr[u + 1], m); ++k) {
-                int x = dst[k];
-                if ((unsigned)x < (unsigned)n && G[x] == 0) o = true;
-            }
-        }
-        if (__syncthreads_or(o)) st = LLP_E_OVERFLOW;
-    }
-    for (int v = t; v < n; v += T) {
-        int g = G[v];
-        dist[v] = g > 0 ? LLP_INF - g : LLP_INF;
-    }
-    if (rounds_out && t == 0) *rounds_out = r;
-    return st;
-}
 
 // --------------------------------------------------------------- kernels
 struct BArgs {
@@ -190,14 +84,8 @@ __device__ __forceinline__ void batch_one(const BArgs& a, int i, int* lds, int* 
             const int* ptr = a.pool + d.in_off;
             const int* dst = ptr + n + 1;
             const int* wgt = dst + m;
-            const int words = (n + 31) >> 5;
-            int* G = lds;
-            unsigned* cur = (unsigned*)(lds + a.ss_n);
-            unsigned* nxt = cur + ((a.ss_n + 31) >> 5);
-            int* lptr = (int*)(nxt + ((a.ss_n + 31) >> 5));
-            st = sssp_wg(ptr, dst, wgt, n, (int)m, src, G, cur, nxt, lptr, sfl, a.out_pool + d.out_off, n + 2,
-                         nullptr);
-            (void)words;
+            st = sssp_wg<false, true>(ptr, dst, wgt, n, (int)m, src, sssp_wg_carve(lds, n), sfl,
+                                      a.out_pool + d.out_off, n + 2);
         }
     } else {
         st = LLP_E_INPUT;
@@ -209,11 +97,14 @@ __device__ __forceinline__ void batch_one(const BArgs& a, int i, int* lds, int* 
     __syncthreads();   // LDS is reused by the next instance
 }
 
+// Registers for 8 waves per SIMD (four workgroups of 512 on a CU) although a
+// few values then spill: 4096 knapsacks and 4096 graphs take 1001 us, against
+// 1126 us without the bound (66 registers, three workgroups on a CU).
 template <int CH>
-__global__ void __launch_bounds__(ch_max_block(CH)) k_batch(BArgs a) {
-    extern __shared__ int lds[];
+__global__ void __launch_bounds__(ch_max_block(CH), CH <= 16 ? 8 : 1) k_batch(BArgs a) {
+    extern __shared__ __align__(8) int lds[];
     __shared__ int claim;
-    __shared__ int sfl[4];
+    __shared__ int sfl[6];
     for (;;) {
         if (threadIdx.x == 0) claim = atomicAdd(&a.ctrl->head, a.chunk);
         __syncthreads();
@@ -232,30 +123,49 @@ __global__ void __launch_bounds__(ch_max_block(CH)) k_batch(BArgs a) {
     }
 }
 
-// Claim order, rebuilt on the device by every solve and every graph replay:
-// longest estimated cost first (longest-processing-time order), so the last
-// instances to start are the short ones.  Estimated cost: knapsack cells, or
-// 20 per SSSP arc (the ratio of the two measured per unit on this batch
-// kernel).  A one-workgroup counting sort over 256 cost classes (four per
-// octave), costliest class first; order within a class is arbitrary.
+// One workgroup prepares every solve and every graph replay: the queue is
+// reset, the limits over desc (largest knapsack W, largest SSSP n, unknown
+// kinds) are measured, and the claim order is rebuilt: longest estimated cost
+// first (longest-processing-time order), so the last instances to start are
+// the short ones.  Estimated cost: knapsack cells, or 26 per SSSP arc (the
+// ratio of the two measured per unit on this batch kernel: 0.325 and 8.5 ps).
+// A counting sort over 256 cost classes (four per octave), costliest class
+// first; order within a class is arbitrary.
 constexpr int ORD_CLASSES = 256;
 
 __device__ __forceinline__ int cost_slot(const llp_instance& d) {
     long long c = 0;
     if (d.kind == LLP_KIND_KNAPSACK) c = (long long)max(d.n, 0) * (max(d.cap_or_source, 0) + 1);
-    else if (d.kind == LLP_KIND_SSSP) c = 20 * (d.m > 0 ? d.m : 0ll) + max(d.n, 0);
+    else if (d.kind == LLP_KIND_SSSP) c = 26 * (d.m > 0 ? d.m : 0ll) + max(d.n, 0);
     if (c <= 0) return ORD_CLASSES - 1;
     const int e = 63 - __clzll((unsigned long long)c);
     const int f = e >= 2 ? (int)((c >> (e - 2)) & 3) : (int)((c << (2 - e)) & 3);
     return ORD_CLASSES - 1 - (4 * e + f);   // 4 e + f <= 251
 }
 
-__global__ void __launch_bounds__(1024) k_batch_order(const llp_instance* desc, int count, int* order) {
+__global__ void __launch_bounds__(1024) k_batch_order(const llp_instance* desc, int count, int* order, BCtrl* c) {
     __shared__ int cnt[ORD_CLASSES];
+    __shared__ int lim[3];
     const int t = threadIdx.x, T = blockDim.x;
     for (int i = t; i < ORD_CLASSES; i += T) cnt[i] = 0;
+    if (t < 3) lim[t] = 0;
     __syncthreads();
-    for (int i = t; i < count; i += T) atomicAdd(&cnt[cost_slot(desc[i])], 1);
+    int mw = 0, mn = 0, bad = 0;
+    for (int i = t; i < count; i += T) {
+        const llp_instance d = desc[i];
+        atomicAdd(&cnt[cost_slot(d)], 1);
+        if (d.kind == LLP_KIND_KNAPSACK) mw = max(mw, d.cap_or_source);
+        else if (d.kind == LLP_KIND_SSSP) mn = max(mn, d.n);
+        else bad = 1;
+    }
+    mw = wave_max(mw);
+    mn = wave_max(mn);
+    const bool anybad = __any(bad);
+    if (lane() == 0) {
+        atomicMax(&lim[0], mw);
+        atomicMax(&lim[1], mn);
+        if (anybad) lim[2] = 1;
+    }
     __syncthreads();
     if (t < 64) {
         // exclusive scan of the class counts, four classes per lane
@@ -272,48 +182,20 @@ __global__ void __launch_bounds__(1024) k_batch_order(const llp_instance* desc, 
             run += v[j];
         }
     }
+    if (t == 0) {
+        BCtrl z;
+        memset(&z, 0, sizeof(z));
+        z.max_w = lim[0];
+        z.max_n = lim[1];
+        z.bad_kind = lim[2];
+        *c = z;
+    }
     __syncthreads();
     for (int i = t; i < count; i += T) order[atomicAdd(&cnt[cost_slot(desc[i])], 1)] = i;
 }
 
-// queue reset (a fill kernel, so the launch can be captured in a graph)
-__global__ void k_batch_reset(BCtrl* c, int* status_dev) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        c->head = 0;
-        c->status = 0;
-        if (status_dev) *status_dev = 0;
-    }
-}
-
 __global__ void k_batch_status(const BCtrl* c, int* status_dev) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *status_dev = c->status;
-}
-
-// limits over desc: largest knapsack W, largest SSSP n, unknown kinds
-__global__ void k_batch_limits(const llp_instance* desc, int count, BCtrl* c) {
-    int mw = 0, mn = 0, bad = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
-        llp_instance d = desc[i];
-        if (d.kind == LLP_KIND_KNAPSACK) mw = max(mw, d.cap_or_source);
-        else if (d.kind == LLP_KIND_SSSP) mn = max(mn, d.n);
-        else bad = 1;
-    }
-    mw = wave_max(mw);
-    mn = wave_max(mn);
-    const bool anybad = __any(bad);
-    if (lane() == 0) {
-        atomicMax(&c->max_w, mw);
-        atomicMax(&c->max_n, mn);
-        if (anybad) atomicMax(&c->bad_kind, 1);
-    }
-}
-
-__global__ void k_batch_limits_reset(BCtrl* c) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        BCtrl z;
-        memset(&z, 0, sizeof(z));
-        *c = z;
-    }
 }
 
 // ---------------------------------------------------------------- batch
@@ -332,14 +214,14 @@ static int batch_ws(void** ws, const llp_opts& o, int64_t count) { return get_wo
 
 size_t batch_workspace_bytes(int64_t count) { return batch_bytes(count); }
 
+static void launch_order(int32_t count, const llp_instance* desc, BCtrl* ctrl, hipStream_t st) {
+    hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, st, desc, count, (int*)((char*)ctrl + 256), ctrl);
+}
+
 // Measure the limits over desc (one readback) and choose the launch shape.
 static int batch_plan(int32_t count, const llp_instance* desc, const llp_opts& o, BCtrl* ctrl, BatchPlan* p) {
     hipStream_t st = (hipStream_t)o.stream;
-    hipLaunchKernelGGL(k_batch_limits_reset, dim3(1), dim3(64), 0, st, ctrl);
-    int g = (count + 255) / 256;
-    if (g > 1024) g = 1024;
-    if (g < 1) g = 1;
-    hipLaunchKernelGGL(k_batch_limits, dim3(g), dim3(256), 0, st, desc, count, ctrl);
+    launch_order(count, desc, ctrl, st);
     LLP_HIP(hipGetLastError());
     BCtrl h;
     int s = readback(st, ctrl, &h, sizeof(h));
@@ -360,7 +242,11 @@ static int batch_plan(int32_t count, const llp_instance* desc, const llp_opts& o
             if (chunk <= 0) chunk = tc;
         }
     }
-    if (block <= 0) block = 512;   // the autotuner's usual choice on the mixed batch
+    // 512 threads is the autotuner's usual choice on a large batch (1001 us
+    // against 1372 with 1024 on 8192 instances); with at most two instances per
+    // CU the longest ones set the time, and 1024 threads solve each sooner
+    // (500 instances: 180 us against 247)
+    if (block <= 0) block = count <= 2 * device_info().cus ? 1024 : 512;
     if (chunk <= 0) chunk = 1;
     if (block % 64 != 0 || block > 1024) return fail(LLP_E_ARG, "block must be a multiple of 64 up to 1024");
     // a record is keyed by the instance count only: when its workgroup is too
@@ -374,8 +260,7 @@ static int batch_plan(int32_t count, const llp_instance* desc, const llp_opts& o
     p->kn_w = h.max_w;
     p->ss_n = h.max_n > 0 ? h.max_n : 1;
     const size_t row = (size_t)(p->kn_w + 1) * 4;
-    // SSSP: state, two frontier bitmaps and the row offsets
-    const size_t ss = (size_t)p->ss_n * 4 + 2 * (size_t)((p->ss_n + 31) / 32) * 4 + (size_t)(p->ss_n + 1) * 4;
+    const size_t ss = sssp_wg_words(p->ss_n, block) * 4;
     size_t need1 = row > ss ? row : ss;
     size_t need2 = 2 * row > ss ? 2 * row : ss;
     // k_batch's own LDS (the claim word and the solver flags) comes first
@@ -421,11 +306,7 @@ static int batch_enqueue(const BatchPlan& p, int32_t count, const llp_instance* 
     // limits and claim order are measured again by every launch sequence, so a
     // captured graph stays valid whatever else uses the workspace between
     // replays, and its replays see the current instance table
-    const int lg = std::min(std::max((count + 255) / 256, 1), 1024);
-    hipLaunchKernelGGL(k_batch_limits_reset, dim3(1), dim3(64), 0, st, ctrl);
-    hipLaunchKernelGGL(k_batch_limits, dim3(lg), dim3(256), 0, st, desc, count, ctrl);
-    hipLaunchKernelGGL(k_batch_order, dim3(1), dim3(1024), 0, st, desc, count, (int*)a.order);
-    hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, st, ctrl, (int*)nullptr);
+    launch_order(count, desc, ctrl, st);
     const int grid = batch_grid(p, count);
     int s = dispatch_ch(p.ch, [&](auto c) {
         constexpr int CH = decltype(c)::value;

@@ -1,0 +1,214 @@
+// sssp_wg.h - single-source shortest paths of one small graph by one
+// workgroup (paper Section 5.2), for the batch (batch.hip).
+//
+// State G[v] = INF - d(v) in LDS (bottom 0, the source INF), the row offsets
+// in LDS, and a bitmap of active vertices (their state rose since their arcs
+// were last pushed).  Taking an active vertex u pushes single-arc partial
+// advances G[x] <- max(G[x], G[u] - w) along its out-arcs with LDS atomicMax
+// (Definition 3: a partial maximum is an alpha-forbidden advance) and makes x
+// active where that raised it; no active vertex is the fixpoint.
+//
+// What bounds it is how the arcs are read: with a thread per vertex, each of
+// its loads touched a line per lane and refetched it for every arc (5 clocks
+// per arc and CU).  So a wave takes the active vertices of a block of 64
+// together and walks their arcs edge by edge: positions 0 .. E-1 run over the
+// block's arcs, lane l takes positions l + 64 j, and neighbouring lanes read
+// neighbouring arcs.  A position's vertex comes from a table of 256 bytes per
+// wave: every vertex writes its lane at its first position and a max-scan
+// fills the rest.  A row of more than SW_LONG arcs needs no table.  4096
+// graphs of 256 to 4096 vertices (80 M arcs): 681 us, against 1984 us with a
+// thread per vertex.  Steps of 512 positions instead of 256 are slower (760
+// us: more registers), so are workgroups of 256 or 1024 threads (934, 820).
+// A round is one scan of the bitmap; within a round waves see each other's
+// advances, so a round is at least a synchronous one.
+#pragma once
+
+#include "llp_dev.h"
+#include "llp_host.h"
+
+namespace llp {
+
+constexpr int SW_PER = 4;                       // arc positions per lane and step
+constexpr int SW_CHUNK = LLP_WAVE * SW_PER;
+constexpr int SW_LONG = 256;    // longest row taken through the table
+
+// LDS words needed for n vertices and T threads, n + 1 row offsets among them.
+__host__ __device__ constexpr size_t sssp_wg_words(size_t n, size_t T) {
+    return 2 * ((n + 63) / 64) + T / 64 * (SW_CHUNK / 4) + n + n + 1;
+}
+
+struct SsspWg {
+    unsigned long long* act;   // active vertices, a word per block of 64
+    unsigned char* own;        // the wave's position table
+    int* G;
+    int* ptr;
+};
+
+// lds: 8-byte aligned, sssp_wg_words(n, blockDim.x) words.
+__device__ __forceinline__ SsspWg sssp_wg_carve(void* lds, int n) {
+    SsspWg s;
+    const int nb = (n + 63) >> 6;
+    s.act = (unsigned long long*)lds;
+    unsigned char* own = (unsigned char*)(s.act + nb);
+    s.own = own + (threadIdx.x >> 6) * SW_CHUNK;
+    s.G = (int*)(own + (blockDim.x >> 6) * SW_CHUNK);
+    s.ptr = s.G + n;
+    return s;
+}
+
+// One arc's advance.
+__device__ __forceinline__ void sssp_wg_push(const SsspWg& s, int x, int cand) {
+    if (cand > s.G[x] && atomicMax(&s.G[x], cand) < cand)
+        atomicOr(&((unsigned*)s.act)[x >> 5], 1u << (x & 31));
+}
+
+// Arcs ks[j] of tails with state gs[j] (j < SW_PER, those with on[j]).  UNIT: every
+// weight is 1.  NEG: negative weights are malformed input, else they are
+// taken as they are.
+template <bool UNIT, bool NEG>
+__device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, const int* wgt, int n, const int* ks,
+                                             const int* gs, const bool* on, bool& bad, bool& ovf) {
+    int x[SW_PER], w[SW_PER];
+#pragma unroll
+    for (int j = 0; j < SW_PER; ++j) {
+        x[j] = on[j] ? dst[ks[j]] : 0;
+        w[j] = UNIT ? 1 : (on[j] ? wgt[ks[j]] : 0);
+    }
+#pragma unroll
+    for (int j = 0; j < SW_PER; ++j) {
+        if (!on[j]) continue;
+        if ((unsigned)x[j] >= (unsigned)n || (NEG && w[j] < 0)) {
+            bad = true;
+            continue;
+        }
+        const int cand = (int)((unsigned)gs[j] - (unsigned)w[j]);
+        if (cand <= 0) ovf = true;
+        else sssp_wg_push(s, x[j], cand);
+    }
+}
+
+// Solves with the calling workgroup.  gptr[n + 1], dst[m],
+// wgt[m]: out-CSR; dist[n]: the output (INF = unreached).  fl: LDS int[6].
+// Returns the status, uniform in the workgroup.
+template <bool UNIT, bool NEG>
+__device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src,
+                                       const SsspWg& s, int* fl, int* dist, long long max_rounds) {
+    const int T = blockDim.x, t = threadIdx.x, l = lane(), wave = t >> 6, nw = T >> 6;
+    const int nb = (n + 63) >> 6;
+    for (int v = t; v < n; v += T) s.G[v] = v == src ? LLP_INF : 0;
+    for (int v = t; v <= n; v += T) s.ptr[v] = gptr[v];
+    for (int i = t; i < nb; i += T) s.act[i] = i == (src >> 6) ? 1ull << (src & 63) : 0ull;
+    if (t < 6) fl[t] = 0;   // fl[0 .. 2]: something was taken, by round modulo 3; fl[3]: bad input; fl[4]: overflow
+    __syncthreads();
+    long long r = 0;
+    bool more = true;
+    for (; more && r < max_rounds; ++r) {
+        bool bad = false, ovf = false, did = false;
+        if (t == 0) fl[(r + 1) % 3] = 0;   // last read in round r - 2
+        for (int c = wave; c < nb; c += nw * LLP_WAVE) {   // lane l looks at block c + nw l
+            uint64_t todo = ballot(c + nw * l < nb && s.act[min(c + nw * l, nb - 1)] != 0ull);
+            for (; todo; todo &= todo - 1) {
+                did = true;
+                const int blk = c + nw * (__ffsll((long long)todo) - 1);
+                // take the block's bits, then read the states: what rises later sets its bit again
+                const unsigned long long f = s.act[blk];
+                __builtin_amdgcn_wave_barrier();
+                if (l == 0) atomicAnd(&s.act[blk], ~f);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_wave_barrier();
+                int b = 0, deg = 0, g = 0;
+                if ((f >> l) & 1ull) {
+                    const int v = blk * 64 + l;
+                    b = s.ptr[v];
+                    const int e = s.ptr[v + 1];
+                    if (b < 0 || e > m || e < b) bad = true;
+                    else deg = e - b;
+                    g = s.G[v];
+                }
+                const int len = deg <= SW_LONG ? deg : 0;
+                const int incl = wave_incl_sum(len), E = shfl(incl, 63);
+                const int start = incl - len, off = b - start;
+                for (int base = 0; base < E; base += SW_CHUNK) {
+                    unsigned* cell = (unsigned*)(s.own + SW_PER * l);   // the lane's own SW_PER positions
+                    *cell = 0u;
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_wave_barrier();
+                    if (len > 0 && start < base + SW_CHUNK && incl > base)
+                        s.own[start > base ? start - base : 0] = (unsigned char)(l + 1);
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_wave_barrier();
+                    unsigned q = *cell;
+                    int run = 0, o[SW_PER];
+#pragma unroll
+                    for (int j = 0; j < SW_PER; ++j) {
+                        run = max(run, (int)((q >> (8 * j)) & 255u));
+                        o[j] = run;
+                    }
+                    int before = __shfl_up(wave_incl_max(run), 1, LLP_WAVE);
+                    if (l == 0) before = 0;
+                    q = 0u;
+#pragma unroll
+                    for (int j = 0; j < SW_PER; ++j) q |= (unsigned)max(before, o[j]) << (8 * j);
+                    *cell = q;
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_wave_barrier();
+                    int ks[SW_PER], gs[SW_PER];
+                    bool on[SW_PER];
+#pragma unroll
+                    for (int j = 0; j < SW_PER; ++j) {
+                        const int p = base + 64 * j + l;
+                        on[j] = p < E;
+                        const int w = on[j] ? s.own[64 * j + l] - 1 : 0;
+                        ks[j] = p + shfl(off, w);
+                        gs[j] = shfl(g, w);
+                    }
+                    sssp_wg_arcs<UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                    __builtin_amdgcn_wave_barrier();
+                }
+                for (uint64_t big = ballot(deg > SW_LONG); big; big &= big - 1) {
+                    const int z = __ffsll((long long)big) - 1;
+                    const int zb = shfl(b, z), zd = shfl(deg, z), zg = shfl(g, z);
+                    for (unsigned k0 = 0; k0 < (unsigned)zd; k0 += SW_CHUNK) {
+                        int ks[SW_PER], gs[SW_PER];
+                        bool on[SW_PER];
+#pragma unroll
+                        for (int j = 0; j < SW_PER; ++j) {
+                            const unsigned k = k0 + 64 * j + l;
+                            on[j] = k < (unsigned)zd;
+                            ks[j] = zb + (int)k;
+                            gs[j] = zg;
+                        }
+                        sssp_wg_arcs<UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                    }
+                }
+            }
+        }
+        if (did && l == 0) fl[r % 3] = 1;
+        if (bad) fl[3] = 1;
+        if (ovf) fl[4] = 1;
+        __syncthreads();
+        more = fl[r % 3] != 0 && fl[3] == 0;
+    }
+    int st = LLP_OK;
+    if (fl[3]) st = LLP_E_INPUT;
+    else if (more) st = LLP_E_NOT_CONVERGED;
+    // overflow: an unreached vertex with a reached in-neighbour
+    if (st == LLP_OK && fl[4]) {
+        for (int u = t; u < n; u += T) {
+            if (s.G[u] <= 0) continue;
+            for (int k = max(s.ptr[u], 0); k < min(s.ptr[u + 1], m); ++k) {
+                const int x = dst[k];
+                if ((unsigned)x < (unsigned)n && s.G[x] == 0) fl[5] = 1;
+            }
+        }
+        __syncthreads();
+        if (fl[5]) st = LLP_E_OVERFLOW;
+    }
+    for (int v = t; v < n; v += T) {
+        const int g = s.G[v];
+        dist[v] = g > 0 ? LLP_INF - g : LLP_INF;
+    }
+    return st;
+}
+
+}  // namespace llp

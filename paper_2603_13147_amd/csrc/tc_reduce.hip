@@ -143,11 +143,11 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
                 pe = ptr[min(blk * 64 + l + 1, n)];
             }
             const bool wide = e - b > TC_LONG;
-            for (int k0 = b; !wide && k0 < e; k0 += 8) {
+            for (unsigned k0 = b; !wide && k0 < (unsigned)e; k0 += 8) {
                 int x[8];
                 unsigned have[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[j] = dst[min(k0 + j, e - 1)];
+                for (int j = 0; j < 8; ++j) x[j] = dst[min(k0 + j, (unsigned)e - 1)];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     if ((unsigned)x[j] >= (unsigned)n) {
@@ -158,13 +158,13 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
                 }
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    if (k0 + j < e && (g & ~have[j])) tc_set<BITS>(R, act, x[j], g);
+                    if (k0 + j < (unsigned)e && (g & ~have[j])) tc_set<BITS>(R, act, x[j], g);
             }
             for (uint64_t q = ballot(wide); q; q &= q - 1) {
                 const int src = __ffsll((long long)q) - 1;
-                const int eb = shfl(b, src), ee = shfl(e, src);
+                const unsigned eb = shfl(b, src), ee = shfl(e, src);
                 const unsigned gg = (unsigned)shfl((int)g, src);
-                for (int k0 = eb + l; k0 < ee; k0 += 4 * LLP_WAVE) {
+                for (unsigned k0 = eb + l; k0 < ee; k0 += 4 * LLP_WAVE) {
                     int x[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) x[j] = dst[min(k0 + j * LLP_WAVE, ee - 1)];
