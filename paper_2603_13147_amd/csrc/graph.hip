@@ -227,7 +227,7 @@ struct GShared {
         int dcb[GW][DBLK + 192];  // dense blocks: candidate (or row) of each position; per row: bound, first arc, first position
         struct {
             int pw[GW][8][64];    // push blocks: entry start, source value, row base, duration; entry of each position
-            int lq_v[512], lq_ob[512], lq_od[512];   // bucketed push rounds: the local queue (see local_drain)
+            int4 lq[512];         // bucketed push rounds: the local queue {vertex, value, first out-arc, out-arcs}
         };
     };
     unsigned long long ctr;    // appends to the phase's main output list
@@ -238,7 +238,7 @@ struct GShared {
     int tmp1;
     int carried;
     int tmp[GW + 1];
-    int lq_top;                // entries of the local queue
+    int lq_top[2];             // entries of the local queue, by parity of the pass
     long long lq_arcs;         // arcs the local passes pushed
     unsigned long long cnt_rd, cnt_gath;   // dense rounds: arcs read, states gathered by the workgroup
 };
@@ -644,17 +644,17 @@ constexpr int PBLK = 64 * PJ;
 // a later round.  The bucket bounds how far a pass can run ahead.
 constexpr int LQ_CAP = 512;
 constexpr int LQ_DEG = 8;
-constexpr int LQ_ITERS = 64;
+constexpr int LQ_ITERS = 32;
+constexpr int LQ_LANES = 4;                // lanes per entry of a pass
+constexpr int LQ_TAKE = GB / LQ_LANES;     // entries per pass at most
 
-// Queue target x (out-row [ob, ob + od)) if it qualifies and there is room;
-// returns whether it was queued.
-__device__ __forceinline__ bool lq_put(GShared& sh, bool want, int x, int ob, int od) {
+// Queue target x advanced to value c (out-row [ob, ob + od)) if it qualifies
+// and there is room; returns whether it was queued.
+__device__ __forceinline__ bool lq_put(GShared& sh, int* top, bool want, int x, int c, int ob, int od) {
     if (!want) return false;
-    const int slot = atomicAdd(&sh.lq_top, 1);
+    const int slot = atomicAdd(top, 1);
     if (slot >= LQ_CAP) return false;
-    sh.lq_v[slot] = x;
-    sh.lq_ob[slot] = ob;
-    sh.lq_od[slot] = od;
+    sh.lq[slot] = make_int4(x, c, ob, od);
     return true;
 }
 
@@ -845,7 +845,7 @@ __device__ void push_wave(const GArgs& a, const Src& src, int wb, int we, int r,
                     ob = a.out_ptr[x[j]];
                     od = a.out_ptr[x[j] + 1] - ob;
                     const bool inb = (long long)(LLP_INF - c[j]) < hi;
-                    if (LQ && lq_put(sh, lq && inb && od > 0 && od <= LQ_DEG, x[j], ob, od)) {
+                    if (LQ && lq_put(sh, &sh.lq_top[0], lq && inb && od > 0 && od <= LQ_DEG, x[j], c[j], ob, od)) {
                         // queued: its arcs are pushed by this workgroup's local passes
                     } else if (cont && cv < 0 && od > 0 && od <= CDEG && (hi <= 0 || inb)) {
                         lmin = min(lmin, dist_key(a, c[j]));
@@ -872,91 +872,107 @@ __device__ void push_wave(const GArgs& a, const Src& src, int wb, int we, int r,
 
 // The local passes of a bucketed push round (see LQ_CAP): called by every
 // thread of the workgroup after its share of the list.  Each pass takes up
-// to GB of the newest entries, one per thread, and pushes the entry's
-// out-arcs (at most LQ_DEG) with the vertex's current value.
+// to LQ_TAKE of the newest entries, LQ_LANES lanes each, and pushes the
+// entry's out-arcs (at most LQ_DEG) with the value it was queued with; an
+// entry whose vertex has risen since is dropped, as whoever raised it queued
+// or listed it again.
+// A pass is bound by its chain of round trips and instructions (on a mesh a
+// workgroup has a few tens of entries), not by its arcs: about 1.7 us now, 5
+// with a thread per entry that waited for each arc's atomic and row bounds in
+// turn.  SSSP on a 2048^2 grid (weights to 1000): 27.7 ms -> 8.6 ms, on a
+// 300^2 grid 2.70 -> 1.17.  (8 lanes per entry: 9.3 and 1.17; at most 64
+// passes a round instead of 32: 9.1, 128: 10.2.)  So a lane has two
+// arcs at most, every load of a stage is issued before any is used, the
+// targets' row bounds come with their states, and a target counts as
+// advanced when the value exceeds the state read: the atomicMax returns
+// nothing and nothing waits for it (two lanes that read the same state may
+// both queue the target; the lower one is dropped later).
+// States are read past the L1, whose lines a launch of many rounds never
+// renews: with zero weights a stale state could look advanced for ever.
 template <bool COH>
 __device__ void local_drain(const GArgs& a, int r, long long hi, const ListRef& out, unsigned long long* ctr,
                             GShared& sh, bool& ovf, long long& nadv, int& lmin) {
+    constexpr int PER = LQ_DEG / LQ_LANES;
+    const int slot = threadIdx.x / LQ_LANES, k0 = threadIdx.x % LQ_LANES;
     long long arcs = 0;
     for (int it = 0;; ++it) {
+        const int par = it & 1;
         __syncthreads();
-        const int top = min(sh.lq_top, LQ_CAP);
+        const int top = min(sh.lq_top[par], LQ_CAP);
         if (top == 0) break;
         // every queued entry may still have to be appended, and a pass can add
         // LQ_DEG - 1 entries per entry it takes: passes run while the
         // workgroup's segment of CL[r] can hold that, else the queue is handed
         // to the list
         const long long room = (long long)out.cap - (long long)(sh.ctr & 0xffffffffull) - top;
-        int take = min(top, GB);
+        int take = min(top, LQ_TAKE);
         if ((long long)take * (LQ_DEG - 1) > room) take = (int)max(room / (LQ_DEG - 1), 0ll);
-        const bool last = it >= LQ_ITERS || take == 0;
-        if (last) take = top;
-        const int base = top - take;
-        // the thread's entries, read before the stack is shortened and refilled
-        int v[2] = {-1, -1}, ob[2] = {0, 0}, od[2] = {0, 0};
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int i = base + threadIdx.x + q * GB;
-            if (i < top) {
-                v[q] = sh.lq_v[i];
-                ob[q] = sh.lq_ob[i];
-                od[q] = sh.lq_od[i];
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) sh.lq_top = base;
-        __syncthreads();
-        if (last) {
-            // hand what is left to the next round
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                bool changed = false;
-                if (v[q] >= 0) {
-                    changed = amax(&a.cstamp[v[q]], r) < r;
-                    lmin = min(lmin, dist_key(a, ld_relaxed(&a.G[v[q]])));
-                }
-                if (changed) nadv++;
-                append<COH>(changed, v[q], ob[q], od[q], ctr, out, &a.ctrl->status);
-            }
-            break;
-        }
-        const int gv = v[0] >= 0 ? ld_relaxed(&a.G[v[0]]) : 0;
-        bool bad = false;
-        int x[LQ_DEG], cand[LQ_DEG];
-#pragma unroll
-        for (int k = 0; k < LQ_DEG; ++k) {
-            const bool act = v[0] >= 0 && k < od[0];
-            const int e = act ? clampi(ob[0] + k, a.m, bad) : 0;
-            x[k] = act ? a.out_dst[e] : 0;
-            const int w = act ? (a.unit_w ? 1 : a.out_w[e]) : 0;
-            bool o = false;
-            const int cc = act ? pull_cand(gv, w, o) : 0;
-            ovf |= act && o;
-            cand[k] = cc;
-            arcs += act ? 1 : 0;
-        }
-        int gx[LQ_DEG];
-#pragma unroll
-        for (int k = 0; k < LQ_DEG; ++k) {
-            x[k] = clampi(x[k], a.n, bad);
-            gx[k] = a.G[x[k]];
-        }
-        if (bad) record_diag(a.ctrl->diag, 67, v[0], ob[0], od[0], a.n);
-#pragma unroll
-        for (int k = 0; k < LQ_DEG; ++k) {
+        if (it >= LQ_ITERS || take == 0) {
+            // hand what is left to the next round (LQ_CAP is at most GB)
             bool changed = false;
-            int yob = 0, yod = 0;
-            if (cand[k] > 0 && cand[k] > gx[k] && amax(&a.G[x[k]], cand[k]) < cand[k]) {
-                yob = a.out_ptr[x[k]];
-                yod = a.out_ptr[x[k] + 1] - yob;
-                const bool inb = (long long)(LLP_INF - cand[k]) < hi;
-                if (!lq_put(sh, inb && yod > 0 && yod <= LQ_DEG, x[k], yob, yod)) {
-                    lmin = min(lmin, dist_key(a, cand[k]));
-                    changed = amax(&a.cstamp[x[k]], r) < r;
-                }
+            int4 en = make_int4(0, 0, 0, 0);
+            if ((int)threadIdx.x < top) {
+                en = sh.lq[threadIdx.x];
+                changed = amax(&a.cstamp[en.x], r) < r;
+                lmin = min(lmin, dist_key(a, max(en.y, ld_relaxed(&a.G[en.x]))));
             }
             if (changed) nadv++;
-            append<COH>(changed && yod > 0, x[k], yob, yod, ctr, out, &a.ctrl->status);
+            append<COH>(changed, en.x, en.z, en.w, ctr, out, &a.ctrl->status);
+            break;
+        }
+        const int base = top - take;
+        // the entry is read before the stack is refilled
+        int4 en = make_int4(-1, 0, 0, 0);
+        if (slot < take) en = sh.lq[base + slot];
+        if (threadIdx.x == 0) sh.lq_top[par ^ 1] = base;
+        __syncthreads();
+        const int gv = en.x >= 0 ? ld_relaxed(&a.G[en.x]) : LLP_INF;
+        bool bad = false;
+        int x[PER], c[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const bool act = k0 + LQ_LANES * j < en.w;
+            const int e = act ? clampi(en.z + k0 + LQ_LANES * j, a.m, bad) : 0;
+            x[j] = act ? a.out_dst[e] : 0;
+            c[j] = act ? (a.unit_w ? 1 : a.out_w[e]) : 0;
+        }
+        const int deg = gv > en.y ? 0 : en.w;   // 0: dropped, it rose since
+        int gx[PER], yb[PER], ye[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const bool act = k0 + LQ_LANES * j < deg;
+            x[j] = clampi(x[j], a.n, bad);
+            gx[j] = act ? ld_relaxed(&a.G[x[j]]) : LLP_INF;
+            yb[j] = act ? a.out_ptr[x[j]] : 0;
+            ye[j] = act ? a.out_ptr[x[j] + 1] : 0;
+            c[j] = act ? pull_cand(en.y, c[j], ovf) : 0;
+            arcs += act ? 1 : 0;
+        }
+        if (bad) record_diag(a.ctrl->diag, 67, en.x, en.z, en.w, a.n);
+        bool far[PER], anyfar = false;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            far[j] = false;
+            if (c[j] <= gx[j]) continue;
+            (void)amax(&a.G[x[j]], c[j]);
+            const int yod = ye[j] - yb[j];
+            const bool inb = (long long)(LLP_INF - c[j]) < hi;
+            if (!lq_put(sh, &sh.lq_top[par ^ 1], inb && yod > 0 && yod <= LQ_DEG, x[j], c[j], yb[j], yod)) {
+                lmin = min(lmin, dist_key(a, c[j]));
+                far[j] = true;
+                anyfar = true;
+            }
+        }
+        if (__any(anyfar)) {
+            int old[PER];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) old[j] = far[j] ? amax(&a.cstamp[x[j]], r) : r;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const bool changed = old[j] < r;
+                if (changed) nadv++;
+                append<COH>(changed && ye[j] > yb[j], x[j], yb[j], ye[j] - yb[j], ctr, out, &a.ctrl->status);
+            }
         }
     }
     if (arcs) atomicAdd((unsigned long long*)&sh.lq_arcs, (unsigned long long)arcs);
@@ -1155,7 +1171,7 @@ __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& 
         sh.cctr = 0ull;
         sh.cmin = LLP_INF;
         sh.carried = 0;
-        sh.lq_top = 0;
+        sh.lq_top[0] = 0;
         sh.lq_arcs = 0;
     }
     __syncthreads();
@@ -1421,13 +1437,16 @@ __global__ void __launch_bounds__(GB, 4) k_graph_step(GArgs a, int k) {
 // pushed), plain loads only as a precheck.  The barrier is correct wherever
 // the workgroups run; only its speed depends on the placement.  The launch
 // hands back to the step launches at the first round that is not a push
-// round of at most TAIL_EDGES arcs (or that the learned network would
-// decide), after TAIL_ROUNDS rounds, or at the end of the sweep, which it
+// round of at most TAIL_EDGES arcs (TAIL_EDGES_LQ in a bucketed round, whose
+// local passes are most of its work and want every CU: a 2048^2 grid takes
+// 15.3 ms with 2^17 for both, 9.5 with 2^15, 9.3 with 2^13 or 2^11, before the
+// passes' last change), or that the learned network would decide, after TAIL_ROUNDS rounds, or at the end of the sweep, which it
 // decodes; it reads and writes the step slot k & 1 of the step launch k
 // that follows it.  Every wait is bounded: a barrier that does not complete
 // within TAIL_SPIN polls sets LLP_E_HIP and ends the launch.
 constexpr int TAIL_XCDS = 8;
 constexpr int TAIL_EDGES = 1 << 17;
+constexpr int TAIL_EDGES_LQ = 1 << 13;   // bucketed rounds: see below
 constexpr int TAIL_ROUNDS = 4096;
 constexpr int TAIL_SPIN = 1 << 22;
 
@@ -1509,7 +1528,7 @@ __global__ void __launch_bounds__(GB, 4) k_graph_tail(GArgs a, int k) {
                 sh.ctr = 0ull;
                 sh.cmin = LLP_INF;
                 sh.carried = 0;
-                sh.lq_top = 0;
+                sh.lq_top[0] = 0;
                 sh.lq_arcs = 0;
             }
         }
@@ -1517,7 +1536,8 @@ __global__ void __launch_bounds__(GB, 4) k_graph_tail(GArgs a, int k) {
         const int code = sh.code;
         // a round's appends (at most one per arc) must fit the participants' segments
         const bool fits = 2ll * sh.tot_edges <= (long long)P * out.cap;
-        if ((code & 3) != MODE_PUSH || sh.tot_edges > TAIL_EDGES || !fits || t >= TAIL_ROUNDS) {
+        const int delta = delta_of(a, code);
+        if ((code & 3) != MODE_PUSH || sh.tot_edges > (delta > 0 ? TAIL_EDGES_LQ : TAIL_EDGES) || !fits || t >= TAIL_ROUNDS) {
             // hand back: the next step launch runs PRE of round r
             if (lead) {
                 c->step_phase[k & 1] = 0;
@@ -1534,7 +1554,6 @@ __global__ void __launch_bounds__(GB, 4) k_graph_tail(GArgs a, int k) {
                 st_i32<true>(out.segmin + sg, LLP_INF);
             }
         }
-        const int delta = delta_of(a, code);
         long long hi = 0;
         if (delta > 0) {
             const int dmin = load_segmin<true>(in.segmin, a.nseg, &sh.tmp1);
@@ -1918,7 +1937,7 @@ static int solve_graph_core(const llp_graph* g, int32_t source, int32_t* out, co
         if (batch < 64) batch *= 2;
         // the last round was a narrow push round: run the next rounds in the tail
         const SchedHist& last = h.hist[h.rounds & 1];
-        if (tail_ok && (h.mode & 3) == MODE_PUSH && last.cl_edges <= TAIL_EDGES) {
+        if (tail_ok && (h.mode & 3) == MODE_PUSH && last.cl_edges <= (lq_kernel ? TAIL_EDGES_LQ : TAIL_EDGES)) {
             hipLaunchKernelGGL(k_graph_tail_reset, dim3(1), dim3(64), 0, st, a.ctrl);
             hipEvent_t t0 = timing ? timing_event(2 + evs.size()) : nullptr;
             hipEvent_t t1 = timing ? timing_event(3 + evs.size()) : nullptr;
