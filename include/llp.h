@@ -59,7 +59,10 @@ typedef enum {
 #define LLP_SCHED_HYBRID  3u  /* per round, a frontier-width threshold: dense when the changed vertices'
                                  out-arcs exceed a fraction of all arcs (SSSP 1/3, BFS 1/14, jobs 1/2),
                                  push otherwise (pull without out_w); on weighted graphs of 2 to 8
-                                 arcs per vertex the push rounds use the wide delta buckets */
+                                 arcs per vertex the push rounds use the wide delta buckets; a small
+                                 graph (at most 16384 vertices and 100000 arcs, 3 or more per vertex) is
+                                 solved by push rounds in one workgroup when nothing but a workspace,
+                                 a stream and the schedule is asked for */
 #define LLP_SCHED_RANDOM  4u  /* per round, a seeded random mode and delta class (schedule-independence tests) */
 #define LLP_SCHED_SCRIPT  5u  /* per round, the code opts->plan[r-1] (plain after the plan ends); used to
                                  measure what a decision at a given round costs when training the scheduler */

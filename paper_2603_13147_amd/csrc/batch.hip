@@ -27,6 +27,7 @@
 namespace llp {
 
 constexpr int SS_MAX_N = 8192;
+constexpr int SS_PER = 4;                  // see sssp_wg.h
 constexpr size_t BATCH_STATIC_LDS = 320;   // bytes of k_batch's static LDS (claim word, flags), rounded up
 
 struct BCtrl {
@@ -84,7 +85,7 @@ __device__ __forceinline__ void batch_one(const BArgs& a, int i, int* lds, int* 
             const int* ptr = a.pool + d.in_off;
             const int* dst = ptr + n + 1;
             const int* wgt = dst + m;
-            st = sssp_wg<false, true>(ptr, dst, wgt, n, (int)m, src, sssp_wg_carve(lds, n), sfl,
+            st = sssp_wg<SS_PER, false, true>(ptr, dst, wgt, n, (int)m, src, sssp_wg_carve<SS_PER>(lds, n), sfl,
                                       a.out_pool + d.out_off, n + 2);
         }
     } else {
@@ -260,7 +261,7 @@ static int batch_plan(int32_t count, const llp_instance* desc, const llp_opts& o
     p->kn_w = h.max_w;
     p->ss_n = h.max_n > 0 ? h.max_n : 1;
     const size_t row = (size_t)(p->kn_w + 1) * 4;
-    const size_t ss = sssp_wg_words(p->ss_n, block) * 4;
+    const size_t ss = sssp_wg_words(p->ss_n, block, SS_PER) * 4;
     size_t need1 = row > ss ? row : ss;
     size_t need2 = 2 * row > ss ? 2 * row : ss;
     // k_batch's own LDS (the claim word and the solver flags) comes first

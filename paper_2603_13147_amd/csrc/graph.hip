@@ -32,6 +32,7 @@
 #include "llp_host.h"
 #include "llp_lists.h"
 #include "llp_sched.h"
+#include "sssp_wg.h"
 
 namespace llp {
 
@@ -1654,6 +1655,38 @@ __global__ void k_graph_decode(int* G, int n) {
     }
 }
 
+// --------------------------------------------------------------- small graphs
+// A graph whose state and row offsets fit in one CU's LDS, solved by one
+// workgroup in one launch (sssp_wg.h): its rounds are separated by a workgroup
+// barrier (about 2 us each) instead of a launch over 512 list segments (10 to
+// 19 us each).  One CU pushes about 0.8 G arcs a second, so the number of
+// arcs sets the limit: uniform graphs of 8 arcs per vertex take 47 us instead
+// of 135 (n = 64), 133 instead of 294 (n = 4096), 284 instead of 336 (n =
+// 12000, 108 K arcs) and 439 instead of 398 (n = 16384, 147 K arcs); R-MAT
+// graphs 153 instead of 215 us (70 K arcs) and 238 instead of 198 (139 K).
+constexpr int SMALL_N = 16384;     // 137 KB of LDS
+constexpr int SMALL_M = 100000;
+constexpr int SMALL_T = 1024;
+constexpr int SMALL_PER = 4;       // 8: 143 us at n = 4096, 12: 162
+
+// Below 3 arcs per vertex a graph may be a chain, through which the grid-wide
+// push rounds walk 32 steps each; weighted meshes want the buckets of the
+// grid-wide rounds (a 64^2 grid: 479 us here, 303 there; 16^2: 49 and 87).
+static bool small_graph(int n, long long m, const SchedParams& sp) {
+    return n <= SMALL_N && m <= SMALL_M && m >= 3ll * n && (sp.push_dclass != DCLS_WIDE || n <= 1024);
+}
+
+template <bool UNIT>
+__global__ void __launch_bounds__(SMALL_T) k_graph_small(int n, int m, const int* out_ptr, const int* out_dst,
+                                                         const int* out_w, int source, int* dist, long long max_rounds,
+                                                         int* status) {
+    __shared__ unsigned long long lds[(sssp_wg_words(SMALL_N, SMALL_T, SMALL_PER) + 1) / 2];
+    __shared__ int fl[6];
+    const int st = sssp_wg<SMALL_PER, UNIT, false>(out_ptr, out_dst, out_w, n, m, source, sssp_wg_carve<SMALL_PER>(lds, n),
+                                                   fl, dist, max_rounds);
+    if (threadIdx.x == 0) *status = st;
+}
+
 // --------------------------------------------------------------- host
 struct GraphLayout {
     int nseg;
@@ -1839,6 +1872,27 @@ static int solve_graph_core(const llp_graph* g, int32_t source, int32_t* out, co
     s = get_workspace(o, need, &ws);
     if (s) return s;
     graph_ws(g->n, g->m, per_cu, &a, (char*)ws, need);
+
+    // Small graphs under the hybrid schedule: one workgroup, one launch, where
+    // the call asks for nothing that belongs to the rounds of the grid-wide sweep.
+    if (o.sched == LLP_SCHED_HYBRID && !jobs_dur && can_push && small_graph(g->n, g->m, a.sp) && o.flags == 0 &&
+        !o.stats && !o.warm_start && !o.abort_host && o.max_rounds <= 0 && o.chunk <= 0 && o.block <= 0) {
+        const long long limit = 4 * (long long)g->n + 64;
+        if (bfs)
+            hipLaunchKernelGGL(k_graph_small<true>, dim3(1), dim3(SMALL_T), 0, st, a.n, a.m, a.out_ptr, a.out_dst, a.out_w,
+                               source, out, limit, (int*)ws);
+        else
+            hipLaunchKernelGGL(k_graph_small<false>, dim3(1), dim3(SMALL_T), 0, st, a.n, a.m, a.out_ptr, a.out_dst, a.out_w,
+                               source, out, limit, (int*)ws);
+        LLP_HIP(hipGetLastError());
+        int h = 0;
+        s = readback(st, ws, &h, sizeof(h));
+        if (s) return s;
+        if (h == LLP_E_INPUT) return fail(h, "a row offset or vertex id is out of range");
+        if (h == LLP_E_OVERFLOW) return fail(h, "a reachable distance does not fit int32");
+        if (h == LLP_E_NOT_CONVERGED) return fail(h, "not converged after %lld rounds", limit);
+        return h ? fail(h, "device status %d", h) : LLP_OK;
+    }
 
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timing = (o.flags & LLP_TIMING) && o.stats;

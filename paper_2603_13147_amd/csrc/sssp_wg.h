@@ -1,5 +1,6 @@
 // sssp_wg.h - single-source shortest paths of one small graph by one
-// workgroup (paper Section 5.2), for the batch (batch.hip).
+// workgroup (paper Section 5.2), shared by the batch (batch.hip) and by small
+// graphs solved alone (graph.hip).
 //
 // State G[v] = INF - d(v) in LDS (bottom 0, the source INF), the row offsets
 // in LDS, and a bitmap of active vertices (their state rose since their arcs
@@ -13,12 +14,13 @@
 // per arc and CU).  So a wave takes the active vertices of a block of 64
 // together and walks their arcs edge by edge: positions 0 .. E-1 run over the
 // block's arcs, lane l takes positions l + 64 j, and neighbouring lanes read
-// neighbouring arcs.  A position's vertex comes from a table of 256 bytes per
+// neighbouring arcs.  A position's vertex comes from a table of 64 PER bytes per
 // wave: every vertex writes its lane at its first position and a max-scan
 // fills the rest.  A row of more than SW_LONG arcs needs no table.  4096
 // graphs of 256 to 4096 vertices (80 M arcs): 681 us, against 1984 us with a
-// thread per vertex.  Steps of 512 positions instead of 256 are slower (760
-// us: more registers), so are workgroups of 256 or 1024 threads (934, 820).
+// thread per vertex.  There PER is 4, for four workgroups per CU (PER = 8
+// needs more registers: 760 us), in workgroups of 512 threads (256: 934 us,
+// 1024: 820).
 // A round is one scan of the bitmap; within a round waves see each other's
 // advances, so a round is at least a synchronous one.
 #pragma once
@@ -28,13 +30,12 @@
 
 namespace llp {
 
-constexpr int SW_PER = 4;                       // arc positions per lane and step
-constexpr int SW_CHUNK = LLP_WAVE * SW_PER;
 constexpr int SW_LONG = 256;    // longest row taken through the table
 
 // LDS words needed for n vertices and T threads, n + 1 row offsets among them.
-__host__ __device__ constexpr size_t sssp_wg_words(size_t n, size_t T) {
-    return 2 * ((n + 63) / 64) + T / 64 * (SW_CHUNK / 4) + n + n + 1;
+// per: arc positions per lane and step, a multiple of 4.
+__host__ __device__ constexpr size_t sssp_wg_words(size_t n, size_t T, size_t per) {
+    return 2 * ((n + 63) / 64) + T / 64 * (LLP_WAVE * per / 4) + n + n + 1;
 }
 
 struct SsspWg {
@@ -44,14 +45,15 @@ struct SsspWg {
     int* ptr;
 };
 
-// lds: 8-byte aligned, sssp_wg_words(n, blockDim.x) words.
+// lds: 8-byte aligned, sssp_wg_words(n, blockDim.x, PER) words.
+template <int PER>
 __device__ __forceinline__ SsspWg sssp_wg_carve(void* lds, int n) {
     SsspWg s;
     const int nb = (n + 63) >> 6;
     s.act = (unsigned long long*)lds;
     unsigned char* own = (unsigned char*)(s.act + nb);
-    s.own = own + (threadIdx.x >> 6) * SW_CHUNK;
-    s.G = (int*)(own + (blockDim.x >> 6) * SW_CHUNK);
+    s.own = own + (threadIdx.x >> 6) * LLP_WAVE * PER;
+    s.G = (int*)(own + (blockDim.x >> 6) * LLP_WAVE * PER);
     s.ptr = s.G + n;
     return s;
 }
@@ -62,20 +64,20 @@ __device__ __forceinline__ void sssp_wg_push(const SsspWg& s, int x, int cand) {
         atomicOr(&((unsigned*)s.act)[x >> 5], 1u << (x & 31));
 }
 
-// Arcs ks[j] of tails with state gs[j] (j < SW_PER, those with on[j]).  UNIT: every
+// Arcs ks[j] of tails with state gs[j] (j < PER, those with on[j]).  UNIT: every
 // weight is 1.  NEG: negative weights are malformed input, else they are
 // taken as they are.
-template <bool UNIT, bool NEG>
+template <int PER, bool UNIT, bool NEG>
 __device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, const int* wgt, int n, const int* ks,
                                              const int* gs, const bool* on, bool& bad, bool& ovf) {
-    int x[SW_PER], w[SW_PER];
+    int x[PER], w[PER];
 #pragma unroll
-    for (int j = 0; j < SW_PER; ++j) {
+    for (int j = 0; j < PER; ++j) {
         x[j] = on[j] ? dst[ks[j]] : 0;
         w[j] = UNIT ? 1 : (on[j] ? wgt[ks[j]] : 0);
     }
 #pragma unroll
-    for (int j = 0; j < SW_PER; ++j) {
+    for (int j = 0; j < PER; ++j) {
         if (!on[j]) continue;
         if ((unsigned)x[j] >= (unsigned)n || (NEG && w[j] < 0)) {
             bad = true;
@@ -90,10 +92,11 @@ __device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, co
 // Solves with the calling workgroup.  gptr[n + 1], dst[m],
 // wgt[m]: out-CSR; dist[n]: the output (INF = unreached).  fl: LDS int[6].
 // Returns the status, uniform in the workgroup.
-template <bool UNIT, bool NEG>
+template <int PER, bool UNIT, bool NEG>
 __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src,
                                        const SsspWg& s, int* fl, int* dist, long long max_rounds) {
     const int T = blockDim.x, t = threadIdx.x, l = lane(), wave = t >> 6, nw = T >> 6;
+    constexpr int CHUNK = LLP_WAVE * PER;
     const int nb = (n + 63) >> 6;
     for (int v = t; v < n; v += T) s.G[v] = v == src ? LLP_INF : 0;
     for (int v = t; v <= n; v += T) s.ptr[v] = gptr[v];
@@ -128,57 +131,60 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
                 const int len = deg <= SW_LONG ? deg : 0;
                 const int incl = wave_incl_sum(len), E = shfl(incl, 63);
                 const int start = incl - len, off = b - start;
-                for (int base = 0; base < E; base += SW_CHUNK) {
-                    unsigned* cell = (unsigned*)(s.own + SW_PER * l);   // the lane's own SW_PER positions
-                    *cell = 0u;
+                for (int base = 0; base < E; base += CHUNK) {
+                    unsigned* cell = (unsigned*)(s.own + PER * l);   // the lane's own PER positions
+#pragma unroll
+                    for (int q = 0; q < PER / 4; ++q) cell[q] = 0u;
                     asm volatile("" ::: "memory");
                     __builtin_amdgcn_wave_barrier();
-                    if (len > 0 && start < base + SW_CHUNK && incl > base)
+                    if (len > 0 && start < base + CHUNK && incl > base)
                         s.own[start > base ? start - base : 0] = (unsigned char)(l + 1);
                     asm volatile("" ::: "memory");
                     __builtin_amdgcn_wave_barrier();
-                    unsigned q = *cell;
-                    int run = 0, o[SW_PER];
+                    int run = 0, o[PER];
 #pragma unroll
-                    for (int j = 0; j < SW_PER; ++j) {
-                        run = max(run, (int)((q >> (8 * j)) & 255u));
+                    for (int j = 0; j < PER; ++j) {
+                        run = max(run, (int)((cell[j / 4] >> (8 * (j & 3))) & 255u));
                         o[j] = run;
                     }
                     int before = __shfl_up(wave_incl_max(run), 1, LLP_WAVE);
                     if (l == 0) before = 0;
-                    q = 0u;
 #pragma unroll
-                    for (int j = 0; j < SW_PER; ++j) q |= (unsigned)max(before, o[j]) << (8 * j);
-                    *cell = q;
+                    for (int q = 0; q < PER / 4; ++q) {
+                        unsigned z = 0u;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) z |= (unsigned)max(before, o[4 * q + j]) << (8 * j);
+                        cell[q] = z;
+                    }
                     asm volatile("" ::: "memory");
                     __builtin_amdgcn_wave_barrier();
-                    int ks[SW_PER], gs[SW_PER];
-                    bool on[SW_PER];
+                    int ks[PER], gs[PER];
+                    bool on[PER];
 #pragma unroll
-                    for (int j = 0; j < SW_PER; ++j) {
+                    for (int j = 0; j < PER; ++j) {
                         const int p = base + 64 * j + l;
                         on[j] = p < E;
                         const int w = on[j] ? s.own[64 * j + l] - 1 : 0;
                         ks[j] = p + shfl(off, w);
                         gs[j] = shfl(g, w);
                     }
-                    sssp_wg_arcs<UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                    sssp_wg_arcs<PER, UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
                     __builtin_amdgcn_wave_barrier();
                 }
                 for (uint64_t big = ballot(deg > SW_LONG); big; big &= big - 1) {
                     const int z = __ffsll((long long)big) - 1;
                     const int zb = shfl(b, z), zd = shfl(deg, z), zg = shfl(g, z);
-                    for (unsigned k0 = 0; k0 < (unsigned)zd; k0 += SW_CHUNK) {
-                        int ks[SW_PER], gs[SW_PER];
-                        bool on[SW_PER];
+                    for (unsigned k0 = 0; k0 < (unsigned)zd; k0 += CHUNK) {
+                        int ks[PER], gs[PER];
+                        bool on[PER];
 #pragma unroll
-                        for (int j = 0; j < SW_PER; ++j) {
+                        for (int j = 0; j < PER; ++j) {
                             const unsigned k = k0 + 64 * j + l;
                             on[j] = k < (unsigned)zd;
                             ks[j] = zb + (int)k;
                             gs[j] = zg;
                         }
-                        sssp_wg_arcs<UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                        sssp_wg_arcs<PER, UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
                     }
                 }
             }
