@@ -261,8 +261,8 @@ int llp_solve_reduce(int64_t n, const uint64_t* x, uint64_t* result, const llp_o
 /* For callers that cannot allocate device memory (code under hipGraph
    capture, tight serving loops, harnesses that forbid allocation): the same
    reduction as llp_solve_reduce with the same arguments and result, calling
-   no allocator.  Its scratch (a counter and one partial per tile, at most
-   2048 tiles: 16,640 bytes) is a static array that each GPU holds until the
+   no allocator.  Its scratch (one partial per tile, at most 2048
+   tiles: 16,640 bytes with a header) is a static array that each GPU holds until the
    process ends; opts->workspace is ignored.  Every call on a GPU uses that
    GPU's one array, so calls that overlap on one GPU (other streams, other
    threads) race and must be serialised by the caller.  LLP_E_ARG when the

@@ -509,7 +509,7 @@ def reduce_sum(x, ws=None, **kw):
     if x.dtype != torch.int64:
         raise LLPError(E_ARG, f"x must hold 64-bit words (int64 tensor or uint64 array), got {x.dtype}")
     x = x.to(device="cuda").contiguous()
-    out = torch.zeros(1, dtype=torch.int64, device="cuda")
+    out = torch.empty(1, dtype=torch.int64, device="cuda")
     if ws is None:
         ws = workspace(KIND_REDUCE, x.numel(), 0)
     o = make_opts(workspace=ws, **kw)

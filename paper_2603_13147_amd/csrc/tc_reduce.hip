@@ -14,8 +14,8 @@
 //
 // Reduction.  The tree of tiles: each workgroup sums one tile of the input
 // (grid-stride, modulo 2^64) and publishes it; the root becomes forbidden once
-// all its children have published, which the last workgroup to arrive at the
-// counter observes, and it advances the root to the sum of the partials.
+// all its children have published, which the launch boundary tells, and the
+// second launch advances it to the sum of the partials.
 #include <string.h>
 
 #include <algorithm>
@@ -262,54 +262,53 @@ int solve_tc(int32_t n, int64_t m, const int32_t* out_ptr, const int32_t* out_ds
 // --------------------------------------------------------------- reduction
 constexpr int RB = 256;
 
-struct RCtrl {
-    unsigned int arrived;
-    unsigned int pad;
-};
-
-__global__ void __launch_bounds__(RB) k_reduce(long long n, const unsigned long long* x,
-                                               unsigned long long* partial, RCtrl* c, unsigned long long* result) {
-    __shared__ unsigned long long ws[RB / LLP_WAVE];
-    __shared__ bool last;
-    unsigned long long s = 0;
-    const long long stride = (long long)gridDim.x * RB * 2;
-    // two independent loads in flight per thread per step
-    for (long long i = (long long)blockIdx.x * RB * 2 + threadIdx.x; i < n; i += stride) {
-        s += x[i];
-        if (i + RB < n) s += x[i + RB];
-    }
+// What bounds the sum is the rate of the reads: 16 bytes per thread and step,
+// consecutive over the whole grid, so that the grid reads the array in order
+// (2 loads in flight per thread, each over its own stretch: 30.8 us at 2^24
+// words, 4: 31.7, 8: 34.3).  A first word off the 16-byte alignment and the
+// last word are added apart.  The tiles are counted by the launch boundary:
+// with a counter whose last arrival sums them, each of the 2048 workgroups'
+// release and acquire flushed its L2, and 2^22 words took 61 us.  Both launches
+// together, from HBM: 13.4 us at 2^22 words, 28.1 us at 2^24 (4.8 TB/s; 76.6 us
+// with the counter and 8-byte loads), 87.7 us at 2^26 (6.1 TB/s; 142 us).
+// Sum over the workgroup, valid in thread 0.
+__device__ __forceinline__ unsigned long long block_sum(unsigned long long s, unsigned long long* ws) {
     s = (unsigned long long)wave_sum64((long long)s);
     if (lane() == 0) ws[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long b = 0;
+    unsigned long long b = 0;
+    if (threadIdx.x == 0)
         for (int k = 0; k < RB / LLP_WAVE; ++k) b += ws[k];
-        __hip_atomic_store(&partial[blockIdx.x], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // publish the tile, then count it (release); the last arrival sees all
-        unsigned prev = __hip_atomic_fetch_add(&c->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        last = prev == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!last) return;
-    // root: sum of the published tiles
-    unsigned long long r = 0;
-    for (int k = threadIdx.x; k < (int)gridDim.x; k += RB)
-        r += __hip_atomic_load(&partial[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    r = (unsigned long long)wave_sum64((long long)r);
-    __syncthreads();
-    if (lane() == 0) ws[threadIdx.x >> 6] = r;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long b = 0;
-        for (int k = 0; k < RB / LLP_WAVE; ++k) b += ws[k];
-        *result = b;
-        c->arrived = 0u;   // ready for the next solve on this workspace
-    }
+    return b;
 }
 
-__global__ void k_reduce_reset(RCtrl* c, int* status_dev) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        c->arrived = 0u;
+__global__ void __launch_bounds__(RB) k_reduce_tiles(long long n, const unsigned long long* x,
+                                                     unsigned long long* partial) {
+    __shared__ unsigned long long ws[RB / LLP_WAVE];
+    unsigned long long s = 0;
+    const long long head = n > 0 && ((uintptr_t)x & 15) ? 1 : 0;
+    const ulonglong2* v = (const ulonglong2*)(x + head);
+    const long long pairs = (n - head) / 2;
+    const long long tid = (long long)blockIdx.x * RB + threadIdx.x, nt = (long long)gridDim.x * RB;
+#pragma unroll 1
+    for (long long i = tid; i < pairs; i += nt) s += v[i].x + v[i].y;
+    if (tid == 0) {
+        if (head) s += x[0];
+        if (head + 2 * pairs < n) s += x[n - 1];
+    }
+    s = block_sum(s, ws);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
+// The root: one workgroup over the published tiles.
+__global__ void __launch_bounds__(RB) k_reduce_root(int tiles, const unsigned long long* partial,
+                                                    unsigned long long* result, int* status_dev) {
+    __shared__ unsigned long long ws[RB / LLP_WAVE];
+    unsigned long long s = 0;
+    for (int k = threadIdx.x; k < tiles; k += RB) s += partial[k];
+    s = block_sum(s, ws);
+    if (threadIdx.x == 0) {
+        *result = s;
         if (status_dev) *status_dev = 0;
     }
 }
@@ -333,7 +332,6 @@ int solve_reduce(int64_t n, const uint64_t* x, uint64_t* result, const llp_opts*
     void* ws = nullptr;
     int s = get_workspace(o, reduce_workspace_bytes(n), &ws);
     if (s) return s;
-    RCtrl* c = (RCtrl*)ws;
     unsigned long long* partial = (unsigned long long*)((char*)ws + 256);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timing = (o.flags & LLP_TIMING) && o.stats;
@@ -342,9 +340,9 @@ int solve_reduce(int64_t n, const uint64_t* x, uint64_t* result, const llp_opts*
         LLP_HIP(hipEventCreate(&ev1));
         LLP_HIP(hipEventRecord(ev0, st));
     }
-    hipLaunchKernelGGL(k_reduce_reset, dim3(1), dim3(64), 0, st, c, (o.flags & LLP_ASYNC) ? o.status_dev : nullptr);
-    hipLaunchKernelGGL(k_reduce, dim3(grid), dim3(RB), 0, st, (long long)n, (const unsigned long long*)x, partial,
-                       c, (unsigned long long*)result);
+    hipLaunchKernelGGL(k_reduce_tiles, dim3(grid), dim3(RB), 0, st, (long long)n, (const unsigned long long*)x, partial);
+    hipLaunchKernelGGL(k_reduce_root, dim3(1), dim3(RB), 0, st, grid, (const unsigned long long*)partial,
+                       (unsigned long long*)result, (o.flags & LLP_ASYNC) ? o.status_dev : nullptr);
     LLP_HIP(hipGetLastError());
     if (timing) LLP_HIP(hipEventRecord(ev1, st));
     if (o.flags & LLP_ASYNC) return LLP_OK;
@@ -368,12 +366,11 @@ int solve_reduce(int64_t n, const uint64_t* x, uint64_t* result, const llp_opts*
 }
 
 // ---------------------------------------------------------------- no-allocation reduction
-// The same reduction with its scratch (the arrival counter and one partial
-// per tile) in a file-scope device array instead of a workspace: for callers
-// that cannot allocate.  Each GPU holds its own copy of the array; its
-// device address is looked up once per device (host code never passes the
+// The same reduction with its scratch (one partial per tile) in a file-scope
+// device array instead of a workspace: for callers that cannot allocate.
+// Each GPU holds its own copy of the array; its device address is looked up once per device (host code never passes the
 // array's name itself to a kernel).  Calls on one GPU share the array, so
-// calls that overlap on one GPU race; every call clears the counter first.
+// calls that overlap on one GPU race; every call writes the partials it reads.
 constexpr int REDUCE_MAX_TILES = 2048;
 constexpr size_t REDUCE_SCRATCH_BYTES = 256 + (size_t)REDUCE_MAX_TILES * 8;
 static __device__ __align__(256) unsigned char scratch[REDUCE_SCRATCH_BYTES];
@@ -408,11 +405,10 @@ int solve_reduce_noalloc(int64_t n, const uint64_t* x, uint64_t* result, const l
     void* sp = nullptr;
     int s = scratch_ptr(&sp);
     if (s) return s;
-    RCtrl* c = (RCtrl*)sp;
     unsigned long long* partial = (unsigned long long*)((char*)sp + 256);
-    hipLaunchKernelGGL(k_reduce_reset, dim3(1), dim3(64), 0, st, c, (o.flags & LLP_ASYNC) ? o.status_dev : nullptr);
-    hipLaunchKernelGGL(k_reduce, dim3(grid), dim3(RB), 0, st, (long long)n, (const unsigned long long*)x, partial,
-                       c, (unsigned long long*)result);
+    hipLaunchKernelGGL(k_reduce_tiles, dim3(grid), dim3(RB), 0, st, (long long)n, (const unsigned long long*)x, partial);
+    hipLaunchKernelGGL(k_reduce_root, dim3(1), dim3(RB), 0, st, grid, (const unsigned long long*)partial,
+                       (unsigned long long*)result, (o.flags & LLP_ASYNC) ? o.status_dev : nullptr);
     LLP_HIP(hipGetLastError());
     if (o.flags & LLP_ASYNC) return LLP_OK;
     LLP_HIP(hipStreamSynchronize(st));
