@@ -54,7 +54,7 @@ struct GCtrl {
     int decoded;        // the launch that found the end decoded G in place
     int carried[2];     // entries carried by the delta filter, by round parity (traced solves)
     int step_phase[2];  // step kernel k: phase[k & 1] 0 = PRE of round step_round + 1, 1 = MAIN of step_round
-                        // (2: MAIN of a BFS dense round evaluated with the bitmap)
+                        // (2: MAIN of a BFS dense round evaluated with the bitmap, 3: of a marked pull round)
     int step_round[2];
     int diag[8];        // first guard event: site, index, bound, context
     long long rounds, cand, edges, adv, xedges, pedges, gath;
@@ -232,7 +232,7 @@ struct GShared {
         };
     };
     unsigned long long ctr;    // appends to the phase's main output list
-    unsigned long long cctr;   // PRE in pull rounds: entries carried into CL[r]
+    unsigned long long cctr;   // PRE in pull rounds: entries carried into CL[r]; MAIN of marked ones: rows evaluated
     int cmin;                  // smallest distance appended to CL[r] by this workgroup
     int tot_edges, tot_count;
     int code;
@@ -357,13 +357,18 @@ struct RowWin {
     int pl, pn, g, ob, oe;
 };
 
-__device__ __forceinline__ RowWin load_rows(const GArgs& a, int v) {
+// mark > 0: a row not stamped with it is no candidate of the round; its state
+// reads as INT_MAX, which nothing improves.
+template <bool MK>
+__device__ __forceinline__ RowWin load_rows(const GArgs& a, int v, int mark) {
     RowWin w{0, 0, 0, 0, 0};
     const int x = v + lane();
     if (x < a.n) {
         w.pl = a.in_ptr[x];
         w.pn = a.in_ptr[x + 1];
         w.g = a.G[x];
+        if constexpr (MK)
+            if (mark > 0 && a.stamp[x] != mark) w.g = 0x7fffffff;
         w.ob = a.out_ptr[x];
         w.oe = a.out_ptr[x + 1];
     }
@@ -452,15 +457,21 @@ __device__ __forceinline__ int row_max(const GArgs& a, int lo, int hi, bool& ovf
 // in-arc lies in the range (rows of up to DLONG arcs are evaluated whole,
 // even past we) and the part inside the range of any longer row.  BM: a BFS
 // round whose tails are looked up in the bitmap instead of gathered.
-template <bool BM>
+// mark > 0: a marked pull round evaluates the rows stamped with it (see
+// MARK_EDGES); nrow: rows evaluated.
+template <bool BM, bool MK>
 __device__ void dense_wave(const GArgs& a, int r, int wb, int we, const ListRef& out, GShared& sh, int* cb,
-                           bool& ovf, long long& nadv, int& lmin, int cap, int dlo, int& nrd, int& nins) {
+                           bool& ovf, long long& nadv, int& lmin, int cap, int dlo, int mark, int& nrd, int& nins,
+                           int& nrow) {
     if (wb >= we) return;
     const int l = lane();
     constexpr bool look = BM;
+    // rows with a state of at least fin_at have no arc to read
+    const bool skips = cap < LLP_INF || (MK && mark > 0);
+    const int fin_at = MK && mark > 0 ? 0x7fffffff : cap;
     DenseSrc ds{a.in_ptr, a.n, a.ctrl->diag};
     int v = ds.locate(wb).s;
-    RowWin R = load_rows(a, v);
+    RowWin R = load_rows<MK>(a, v, mark);
     bool first = true;
     while (v < a.n) {
         const int P0 = shfl(R.pl, 0), P1 = shfl(R.pn, 0);
@@ -469,7 +480,7 @@ __device__ void dense_wave(const GArgs& a, int r, int wb, int we, const ListRef&
         if (first && P0 < wb) {
             // row v starts in an earlier wave's range: only a long row has a part here
             first = false;
-            const RowWin Rn = load_rows(a, v + 1);
+            const RowWin Rn = load_rows<MK>(a, v + 1, mark);
             if (d0 > DLONG) {
                 const int g0 = shfl(R.g, 0);
                 const int x = g0 >= cap ? 0 : row_max<BM>(a, wb, min(we, P1), ovf, cap, v, true, arc_bound(g0, dlo), nrd, nins);
@@ -481,10 +492,11 @@ __device__ void dense_wave(const GArgs& a, int r, int wb, int we, const ListRef&
         }
         first = false;
         // a row at the bound is final (see dense_cap): none of its arcs is read
-        if (d0 > DBLK && !(cap < LLP_INF && shfl(R.g, 0) >= cap)) {
-            const RowWin Rn = load_rows(a, v + 1);
+        if (d0 > DBLK && !(skips && shfl(R.g, 0) >= fin_at)) {
+            const RowWin Rn = load_rows<MK>(a, v + 1, mark);
             const int hi = d0 <= DLONG ? P1 : min(we, P1);
             const int g0 = shfl(R.g, 0);
+            if constexpr (MK) nrow += l == 0 ? 1 : 0;
             const int x = g0 >= cap ? 0 : row_max<BM>(a, P0, hi, ovf, cap, v, hi != P1, arc_bound(g0, dlo), nrd, nins);
             row_advance(a, r, v, x, shfl(R.g, 0), shfl(R.ob, 0), shfl(R.oe, 0), hi == P1, out, sh, nadv, lmin);
             R = Rn;
@@ -495,16 +507,17 @@ __device__ void dense_wave(const GArgs& a, int r, int wb, int we, const ListRef&
         // arcs to read number at most DBLK: a final row has none, so the
         // block's positions 0 .. C-1 run over the other rows' arcs in order
         // (row l from position cs)
-        const bool finl = cap < LLP_INF && v + l < a.n && R.g >= cap;
+        const bool finl = skips && v + l < a.n && R.g >= fin_at;
         const int len = (v + l < a.n && !finl) ? R.pn - R.pl : 0;
-        const int incl = cap < LLP_INF ? wave_incl_sum(len) : R.pn - P0;   // no final rows: arcs in order
+        const int incl = skips ? wave_incl_sum(len) : R.pn - P0;   // no final rows: arcs in order
         const bool ok = v + l < a.n && R.pl < we && incl <= DBLK;
         const uint64_t stop = ~ballot(ok);
         const int k = stop ? __ffsll((long long)stop) - 1 : 64;   // >= 1: row v qualifies
         const int C = shfl(incl, k - 1);
         const int cs = incl - len;
-        const RowWin Rn = load_rows(a, v + k);
+        const RowWin Rn = load_rows<MK>(a, v + k, mark);
         const uint64_t fin = ballot(l < k && finl);
+        if constexpr (MK) nrow += l < k && len > 0 ? 1 : 0;
         // weighted graphs: each row's arc bound (see dense_dmin), when any
         // row of the block has one
         const int thr = l < k ? arc_bound(R.g, dlo) : 0x7fffffff;
@@ -1003,13 +1016,42 @@ __device__ __forceinline__ bool carry_step(const GArgs& a, const EdgeCtx& c, int
     return shfl(carry ? 1 : 0, c.j) != 0;
 }
 
-// Expansion: stamp out-neighbours for round r and append new candidates to WL.
-__device__ __forceinline__ void expand_body(const GArgs& a, const EdgeCtx& c, int r, GShared& sh, bool skip) {
+// Marked pull rounds.  Appending a candidate once takes an atomic on its
+// stamp, and atomics go to memory: an expansion of 1.2 M arcs that found 174 k
+// candidates took 60 us, nearly all of it their stamps (3.8 G/s), and the
+// evaluation's two atomics per advanced row as much again.  So an expansion of
+// at least MARK_EDGES arcs (and n / MARK_ROWS) stamps with plain stores, which
+// repeat without harm, and lists nothing; the next launch evaluates the
+// stamped rows the way a dense round does, each row by one wave that is its
+// only writer.  That reads every row's bounds and stamp, and splits the rows
+// evenly by arcs only as far as the stamped ones are spread evenly, hence the
+// two limits.  Plain SSSP on a power-law graph of 4.4 M arcs: 1270 -> 959 us
+// (expansion of its widest rounds 80 -> 30, evaluation 100 -> 55), of 18 M
+// 2720 -> 2050, of 71 M 10.2 -> 7.9 ms, plain BFS on 18 M 2200 -> 1690.  Limits
+// of 2^13 to 2^16 arcs and n / 32 to n / 8 measure alike (965 to 980 on the
+// first graph): the larger ones, so that a round with few candidates of a
+// large graph never reads every row.
+// Not with delta buckets: an entry carried into CL[r] must not be appended
+// again.
+constexpr int MARK_EDGES = 1 << 16;
+constexpr int MARK_ROWS = 8;
+constexpr int MARK_MIN_M = 1 << 18;   // smallest graph that takes the kernel with marked rounds
+__device__ __forceinline__ bool marked_round(const GArgs& a, int mode, long long hi, int edges) {
+    return mode == MODE_PULL && hi <= 0 && edges >= MARK_EDGES && edges >= a.n / MARK_ROWS;
+}
+
+// Expansion: stamp out-neighbours for round r and append new candidates to WL
+// (marks: only stamp them, see above).
+template <bool MK>
+__device__ __forceinline__ void expand_body(const GArgs& a, const EdgeCtx& c, int r, GShared& sh, bool skip,
+                                            bool marks) {
     bool fresh = false;
     int x = 0, rb = 0, d = 0;
     if (c.active && !skip) {
         x = guard(a.out_dst[guard(c.csr, a.m, a.ctrl->diag, 51, c.own.y, c.own.z)], a.n, a.ctrl->diag, 52);
-        if (a.stamp[x] < r && amax(&a.stamp[x], r) < r) {
+        if (MK && marks) {
+            if (a.stamp[x] < r) a.stamp[x] = r;
+        } else if (a.stamp[x] < r && amax(&a.stamp[x], r) < r) {
             rb = a.in_ptr[x];
             d = a.in_ptr[x + 1] - rb;
             fresh = d > 0;
@@ -1114,7 +1156,7 @@ __device__ void bm_prepare(const GArgs& a, int r, int cap, const ListRef& in, co
 // whose evaluation follows in the same launch, else -1.  k: step launch.
 // BM: a bounded BFS dense round prepares the bitmap here and is evaluated by
 // the next launch.
-template <bool LQ, bool BM>
+template <bool LQ, bool BM, bool MK>
 __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& sh, const SegRegs& sin) {
     const ListRef in = cl_of(a, r - 1);
     const ListRef out = cl_of(a, r);
@@ -1187,6 +1229,7 @@ __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& 
     // the same bound the evaluation computes from the same list (dense_cap)
     const int bcap = (BM && mode == MODE_DENSE && !(r == 1 && a.warm_dense)) ? dense_cap(a, r, sh) : LLP_INF;
     const bool bmr = bcap != LLP_INF;
+    const bool marks = MK && marked_round(a, mode, hi, sh.tot_edges);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         GCtrl* c = a.ctrl;
         c->mode = code;
@@ -1194,7 +1237,7 @@ __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& 
         // the next step launch: MAIN of a pull round or of a bitmap dense
         // round, else PRE of the next round (a dense round is evaluated in
         // this launch)
-        c->step_phase[(k + 1) & 1] = mode == MODE_PULL ? 1 : (bmr ? 2 : 0);
+        c->step_phase[(k + 1) & 1] = marks ? 3 : (mode == MODE_PULL ? 1 : (bmr ? 2 : 0));
         c->step_round[(k + 1) & 1] = r;
         if (a.plog && k < a.plog_cap) a.plog[k] = 0;
         c->adv += sh.tot_count;
@@ -1234,7 +1277,7 @@ __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& 
     if (mode == MODE_PULL) {
         for_edges(src, wb, we, own, [&](const EdgeCtx& c) {
             bool skip = carry_step(a, c, r, hi, out, &sh.cctr, sh);
-            expand_body(a, c, r, sh, skip);
+            expand_body<MK>(a, c, r, sh, skip, marks);
         });
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -1296,9 +1339,11 @@ __device__ int dense_dmin(const GArgs& a, int r, GShared& sh) {
 // that must change nothing.
 // bmr: a BFS dense round whose PRE launch built the bitmap and carried the
 // entries above dmin into CL[r] (this launch appends after them); BM: the
-// kernel evaluates every dense round so (see bm_prepare).
-template <bool BM>
-__device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, int k, GShared& sh, int round_code, bool bmr) {
+// kernel evaluates every dense round so (see bm_prepare).  marks: a pull round
+// whose PRE launch stamped the candidates (see MARK_EDGES).
+template <bool BM, bool MK>
+__device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, int k, GShared& sh, int round_code, bool bmr,
+                                           bool marks) {
     const int code = verify ? MODE_DENSE : round_code;
     const int mode = code & 3;
     if (!verify && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1315,17 +1360,18 @@ __device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, in
         sh.cmin = (cont && out.segmin) ? out.segmin[blockIdx.x] : LLP_INF;
         sh.cnt_rd = 0ull;
         sh.cnt_gath = 0ull;
+        if constexpr (MK) sh.cctr = 0ull;
     }
     int* own = sh.own[threadIdx.x >> 6];
     bool ovf = false;
     long long nadv = 0;
     int wb, we;
-    if (mode == MODE_DENSE) {
+    if (mode == MODE_DENSE || (MK && marks)) {
         __syncthreads();
-        const bool bounded = !verify && !(r == 1 && a.warm_dense);
+        const bool bounded = !verify && !(MK && marks) && !(r == 1 && a.warm_dense);
         const int cap = bounded ? dense_cap(a, r, sh) : LLP_INF;
         const int dlo = bounded ? dense_dmin(a, r, sh) : -1;
-        if (blockIdx.x == 0 && threadIdx.x == 0 && !verify) {
+        if (blockIdx.x == 0 && threadIdx.x == 0 && !verify && !(MK && marks)) {
             a.ctrl->cand += a.n;
             if (cap == LLP_INF && dlo < 0) {   // with a bound, the waves count what they read
                 a.ctrl->edges += a.m;
@@ -1335,26 +1381,39 @@ __device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, in
         int rr = verify ? r + 1 : r;
         wave_range(a.m, wb, we);
         int lmin = LLP_INF;
-        int nrd = 0, nins = 0;
+        int nrd = 0, nins = 0, nrow = 0;
         if (BM && !bmr && !verify) {
             // the bitmap kernel runs only sweeps whose dense rounds are all
             // bounded (BFS without a warm start): an unbounded one is a fault
             if (blockIdx.x == 0 && threadIdx.x == 0) set_status(&a.ctrl->status, LLP_E_HIP);
         } else {
-            dense_wave<BM>(a, rr, wb, we, out, sh, sh.dcb[threadIdx.x >> 6], ovf, nadv, lmin, cap, dlo, nrd, nins);
+            dense_wave<BM, MK>(a, rr, wb, we, out, sh, sh.dcb[threadIdx.x >> 6], ovf, nadv, lmin, cap, dlo, MK && marks ? r : 0, nrd, nins, nrow);
         }
-        if ((cap != LLP_INF || dlo >= 0) && !verify) {
+        if ((cap != LLP_INF || dlo >= 0 || (MK && marks)) && !verify) {
             // arcs read and states gathered: summed per workgroup in LDS, one
-            // atomic each per workgroup
+            // atomic each per workgroup (a marked round's rows evaluated as well)
             const long long rd = wave_sum64(nrd), tot = wave_sum64(nins);
             if (lane() == 0) {
                 atomicAdd(&sh.cnt_rd, (unsigned long long)rd);
                 atomicAdd(&sh.cnt_gath, (unsigned long long)tot);
             }
+            if constexpr (MK) {
+                const long long rows = wave_sum64(nrow);
+                if (lane() == 0) atomicAdd(&sh.cctr, (unsigned long long)rows);
+            }
             __syncthreads();
             if (threadIdx.x == 0) {
                 if (sh.cnt_rd) atomicAdd((unsigned long long*)&a.ctrl->edges, sh.cnt_rd);
                 if (sh.cnt_gath) atomicAdd((unsigned long long*)&a.ctrl->gath, sh.cnt_gath);
+                if constexpr (MK) {
+                    if (marks && sh.cctr) {
+                        atomicAdd((unsigned long long*)&a.ctrl->cand, sh.cctr);
+                        if (a.trace && r - 1 < a.trace_cap) {
+                            atomicAdd(&a.trace[r - 1].out_count, (int)sh.cctr);
+                            atomicAdd((unsigned long long*)&a.trace[r - 1].out_edges, sh.cnt_rd);
+                        }
+                    }
+                }
             }
         }
         if (out.segmin) wave_min_to_lds(true, lmin, &sh.cmin);
@@ -1399,7 +1458,9 @@ __device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, in
 // have bucketed rounds; without them a bucketed push round continues chains
 // instead, and the kernel is smaller, which the dense rounds measurably
 // prefer).
-template <bool LQ, bool BM>
+// MK: with marked pull rounds (likewise: small graphs and meshes have none, and
+// their many short launches take 1% longer in the larger kernel).
+template <bool LQ, bool BM, bool MK>
 __global__ void __launch_bounds__(GB, 4) k_graph_step(GArgs a, int k) {
     __shared__ GShared sh;
     // one round trip for the launch's control words and the totals of both
@@ -1416,12 +1477,12 @@ __global__ void __launch_bounds__(GB, 4) k_graph_step(GArgs a, int k) {
     int r = rr, code;
     if (ph == 0) {
         r = rr + 1;
-        code = pre_phase<LQ, BM>(a, r, k, sh, (rr & 1) ? s1 : s0);   // CL[r-1] = CL[rr]
+        code = pre_phase<LQ, BM, MK>(a, r, k, sh, (rr & 1) ? s1 : s0);   // CL[r-1] = CL[rr]
         if (code < 0) return;
     } else {
         code = a.ctrl->mode;
     }
-    main_phase<BM>(a, r, 0, k, sh, code, ph == 2);
+    main_phase<BM, MK>(a, r, 0, k, sh, code, ph == 2, MK && ph == 3);
 }
 
 // --------------------------------------------------------------- tail
@@ -1612,7 +1673,7 @@ __global__ void k_graph_tail_reset(GCtrl* c) {
 
 __global__ void __launch_bounds__(GB) k_graph_verify(GArgs a, int r) {
     __shared__ GShared sh;
-    main_phase<false>(a, r, 1, 0, sh, MODE_DENSE, false);
+    main_phase<false, false>(a, r, 1, 0, sh, MODE_DENSE, false, false);
 }
 
 // --------------------------------------------------------------- finish
@@ -1789,11 +1850,13 @@ static bool coop_supported() {
     return ok;
 }
 
-// lq: the kernel with local queues; bm: BFS dense rounds with the bitmap
-static void launch_step(const GArgs& a, int k, bool lq, bool bm, hipStream_t st) {
-    if (lq) hipLaunchKernelGGL((k_graph_step<true, false>), dim3(a.nseg), dim3(GB), 0, st, a, k);
-    else if (bm) hipLaunchKernelGGL((k_graph_step<false, true>), dim3(a.nseg), dim3(GB), 0, st, a, k);
-    else hipLaunchKernelGGL((k_graph_step<false, false>), dim3(a.nseg), dim3(GB), 0, st, a, k);
+// lq: the kernel with local queues; bm: BFS dense rounds with the bitmap; mk:
+// marked pull rounds
+static void launch_step(const GArgs& a, int k, bool lq, bool bm, bool mk, hipStream_t st) {
+    if (lq) hipLaunchKernelGGL((k_graph_step<true, false, false>), dim3(a.nseg), dim3(GB), 0, st, a, k);
+    else if (bm) hipLaunchKernelGGL((k_graph_step<false, true, false>), dim3(a.nseg), dim3(GB), 0, st, a, k);
+    else if (mk) hipLaunchKernelGGL((k_graph_step<false, false, true>), dim3(a.nseg), dim3(GB), 0, st, a, k);
+    else hipLaunchKernelGGL((k_graph_step<false, false, false>), dim3(a.nseg), dim3(GB), 0, st, a, k);
 }
 
 static int launch_grid_1d(int64_t work) {
@@ -1940,8 +2003,14 @@ static int solve_graph_core(const llp_graph* g, int32_t source, int32_t* out, co
     // the step kernel with local queues where bucketed push rounds can occur
     const bool lq_kernel = !jobs_dur && (a.sp.push_dclass == DCLS_WIDE || o.sched == LLP_SCHED_RANDOM ||
                                          o.sched == LLP_SCHED_SCRIPT || (o.sched == LLP_SCHED_FIXED && o.delta > 0));
+    // marked pull rounds: schedules whose every round may be a pull round, on
+    // graphs dense and large enough for a round of MARK_EDGES and n / MARK_ROWS
+    // arcs to come (a mesh has 4 arcs a vertex and never one)
+    const bool mk_kernel = (o.sched == LLP_SCHED_PLAIN || (o.sched == LLP_SCHED_FIXED && o.delta <= 0 &&
+                                                           !(o.flags & (LLP_DENSE | LLP_PUSH)))) &&
+                           g->m >= MARK_MIN_M && g->m / 6 >= g->n;
     // BFS sweeps: bounded dense rounds look tails up in a bitmap
-    const bool bm_kernel = bfs && !jobs_dur && !lq_kernel && !o.warm_start;
+    const bool bm_kernel = bfs && !jobs_dur && !lq_kernel && !o.warm_start && !mk_kernel;
     // the multi-round tail: push rounds (hybrid, fixed push, learned), graphs
     // whose grid splits evenly over the XCDs, a device with cooperative launches
     bool tail_ok = !jobs_dur && a.nseg % TAIL_XCDS == 0 && a.sp.can_push &&
@@ -1960,12 +2029,12 @@ static int solve_graph_core(const llp_graph* g, int32_t source, int32_t* out, co
                 hipEvent_t e1 = timing_event(3 + evs.size());
                 if (!e0 || !e1) return fail(LLP_E_HIP, "hipEventCreate failed");
                 LLP_HIP(hipEventRecord(e0, st));
-                launch_step(a, (int)k, lq_kernel, bm_kernel, st);
+                launch_step(a, (int)k, lq_kernel, bm_kernel, mk_kernel, st);
                 LLP_HIP(hipEventRecord(e1, st));
                 evs.push_back(e0);
                 evs.push_back(e1);
             } else {
-                launch_step(a, (int)k, lq_kernel, bm_kernel, st);
+                launch_step(a, (int)k, lq_kernel, bm_kernel, mk_kernel, st);
             }
         }
         // without verification, the step launch that finds the end decodes
