@@ -1757,6 +1757,14 @@ struct GraphLayout {
 // per_cu: workgroups (= list segments) per CU, opts->chunk for graph solves;
 // the default 2 keeps every workgroup of a phase kernel resident at once.
 static int graph_wgs_per_cu(int chunk) { return chunk > 0 ? (chunk > 8 ? 8 : chunk) : 2; }
+// A graph of fewer arcs than this runs one workgroup per CU where the library
+// chooses: its rounds are short, and a launch of half the workgroups scans half
+// the list segments and ends sooner.  Hybrid and plain, SSSP and BFS, one per CU
+// against two: power-law graphs of 0.28 M arcs 192 / 457 / 140 / 395 us against
+// 197 / 501 / 149 / 428, of 0.56 M 211 / 504 / 142 / 421 against 219 / 548 / 150 /
+// 451, a mesh of 0.36 M 0.95 and 3.7 ms against 0.97 and 4.4; of 1.1 M arcs 234 /
+// 618 / 154 / 537 against 230 / 643 / 160 / 561, of 4.5 M 330 / 1017 against 318 / 985.
+constexpr int64_t GRAPH_NARROW_M = 1 << 20;
 // workgroups per CU the autotuner tries (llp_autotune_graph); a solve that
 // leaves the choice to the library (chunk 0) takes the record of its size
 // class, so workspaces sized for chunk 0 hold every candidate
@@ -1926,11 +1934,15 @@ static int solve_graph_core(const llp_graph* g, int32_t source, int32_t* out, co
     hybrid_params(jobs_dur ? LLP_KIND_JOBS : (bfs ? LLP_KIND_BFS : LLP_KIND_SSSP), g->n, g->m, can_push, &a.sp);
 
     int per_cu = graph_wgs_per_cu(o.chunk);
+    int need_cu = per_cu;   // the scratch asked for; that of fewer segments is never larger
     if (o.chunk <= 0 && !jobs_dur) {
         int tb = 0, tc = 0;
-        if (tune_lookup(bfs ? LLP_KIND_BFS : LLP_KIND_SSSP, g->m, &tb, &tc)) per_cu = std::min(std::max(tc, 1), GRAPH_TUNE_MAX);
+        if (tune_lookup(bfs ? LLP_KIND_BFS : LLP_KIND_SSSP, g->m, &tb, &tc))
+            per_cu = need_cu = std::min(std::max(tc, 1), GRAPH_TUNE_MAX);
+        else if (g->m < GRAPH_NARROW_M)
+            per_cu = 1;
     }
-    size_t need = graph_ws(g->n, g->m, per_cu, nullptr, nullptr, 0);
+    size_t need = graph_ws(g->n, g->m, need_cu, nullptr, nullptr, 0);
     void* ws = nullptr;
     s = get_workspace(o, need, &ws);
     if (s) return s;
