@@ -221,7 +221,7 @@ constexpr int DSHORT = 64;    // longest row reduced by a single lane
 constexpr int DLONG = 1024;   // longest row evaluated by a single wave
 
 struct GShared {
-    int cnt[MAX_SEG];
+    int cpre[MAX_SEG + 1];
     int epre[MAX_SEG + 1];
     union {
         int own[GW][64];      // list iterator: owner slots
@@ -1117,7 +1117,7 @@ __device__ void bm_prepare(const GArgs& a, int r, int cap, const ListRef& in, co
             if (l == 0 && c + j * W < words) a.bm[c + j * W] = b;
         }
     }
-    const int cnt = min(sh.cnt[blockIdx.x], in.cap);
+    const int cnt = min(sh.cpre[blockIdx.x + 1] - sh.cpre[blockIdx.x], in.cap);
     const int4* ent = in.ent + (long long)blockIdx.x * in.cap;
     int dmn = LLP_INF;
     for (int base = 0; base < cnt; base += BM_CARRY * GB) {
@@ -1168,7 +1168,7 @@ __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& 
         wl = mlp_load(a.sp.mlp);
         hprev = a.ctrl->hist[(r + 1) & 1];
     }
-    seg_scan(sin, a.nseg, sh.cnt, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);   // totals of CL[r-1]
+    seg_scan(sin, a.nseg, sh.cpre, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);   // totals of CL[r-1]
     const int force_dense = (r == 1 && a.warm_dense);
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.trace && r >= 2 && r - 2 < a.trace_cap) {
         // entries the previous round's delta filter carried
@@ -1267,7 +1267,7 @@ __device__ __forceinline__ int pre_phase(const GArgs& a, int r, int k, GShared& 
         }
         return code;   // evaluated by the caller in this launch
     }
-    SegView sv{in.ent, in.cap, a.nseg, sh.cnt, sh.epre, sh.tot_edges, sh.tot_count};
+    SegView sv{in.ent, in.cap, a.nseg, sh.cpre, sh.epre, sh.tot_edges, sh.tot_count};
     ListSrc src{sv, a.ctrl->diag};
     int wb, we;
     wave_range(sh.tot_edges, wb, we);
@@ -1418,7 +1418,7 @@ __device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, in
         }
         if (out.segmin) wave_min_to_lds(true, lmin, &sh.cmin);
     } else {
-        load_segments(a.wl.seg, a.nseg, sh.cnt, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);
+        load_segments(a.wl.seg, a.nseg, sh.cpre, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             a.ctrl->cand += sh.tot_count;
             a.ctrl->edges += sh.tot_edges;
@@ -1430,7 +1430,7 @@ __device__ __forceinline__ void main_phase(const GArgs& a, int r, int verify, in
                 a.trace[r - 1].out_edges = sh.tot_edges;
             }
         }
-        SegView sv{a.wl.ent, a.wl.cap, a.nseg, sh.cnt, sh.epre, sh.tot_edges, sh.tot_count};
+        SegView sv{a.wl.ent, a.wl.cap, a.nseg, sh.cpre, sh.epre, sh.tot_edges, sh.tot_count};
         ListSrc src{sv, a.ctrl->diag};
         wave_range(sh.tot_edges, wb, we);
         for_edges(src, wb, we, own, [&](const EdgeCtx& c) { eval_body(a, c, r, out, sh, ovf, nadv); });
@@ -1550,7 +1550,7 @@ __global__ void __launch_bounds__(GB, 4) k_graph_tail(GArgs a, int k) {
     for (int t = 0;; ++t, ++r) {
         const ListRef in = cl_of(a, r - 1);
         const ListRef out = cl_of(a, r);
-        load_segments<true>(in.seg, a.nseg, sh.cnt, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);
+        load_segments<true>(in.seg, a.nseg, sh.cpre, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);
         if (sh.tot_count == 0) {
             // the end of the sweep: decode G as the step launch that finds it does
             if (lead) {
@@ -1647,7 +1647,7 @@ __global__ void __launch_bounds__(GB, 4) k_graph_tail(GArgs a, int k) {
                 a.trace[r - 1] = tr;
             }
         }
-        SegView sv{in.ent, in.cap, a.nseg, sh.cnt, sh.epre, sh.tot_edges, sh.tot_count};
+        SegView sv{in.ent, in.cap, a.nseg, sh.cpre, sh.epre, sh.tot_edges, sh.tot_count};
         ListSrcT<true> src{sv, c->diag};
         const int wb = (int)((long long)sh.tot_edges * w / W), we = (int)((long long)sh.tot_edges * (w + 1) / W);
         bool ovf = false;

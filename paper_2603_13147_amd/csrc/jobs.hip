@@ -81,7 +81,7 @@ struct JArgs {
 };
 
 struct JShared {
-    int cnt[J_MAX_SEG];
+    int cpre[J_MAX_SEG + 1];
     int epre[J_MAX_SEG + 1];
     int own[JW][64];
     unsigned long long ctr;
@@ -226,7 +226,7 @@ __device__ void jobs_narrow(const JArgs& a, int k, int r, const ListRef& in, int
     __syncthreads();
     // stage R[r-1] into q[0] (entries in any segments, in any order)
     for (int sg = t; sg < a.nseg; sg += JB) {
-        const int cs = min(sh.cnt[sg], in.cap);
+        const int cs = min(sh.cpre[sg + 1] - sh.cpre[sg], in.cap);
         if (cs > 0) {
             const int b = atomicAdd(&sh.qn[0], cs);
             for (int i = 0; i < cs; ++i) sh.q[0][b + i] = in.ent[(long long)sg * in.cap + i];
@@ -343,7 +343,7 @@ __global__ void __launch_bounds__(JB) k_jobs_level(JArgs a, int k) {
     if (ld_relaxed(&c->done) || ld_relaxed(&c->status)) return;
     const int r = c->lvl[k & 1], si = c->src[k & 1];
     const ListRef in = si == 0 ? jl_of(a, r - 1) : (si == 1 ? a.h0 : a.h1);
-    load_segments(in.seg, a.nseg, sh.cnt, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);
+    load_segments(in.seg, a.nseg, sh.cpre, sh.epre, sh.tmp, &sh.tot_edges, &sh.tot_count);
     if (sh.tot_count == 0) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             c->done = 1;
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(JB) k_jobs_level(JArgs a, int k) {
         c->src[(k + 1) & 1] = 0;
     }
     __syncthreads();
-    SegView sv{in.ent, in.cap, a.nseg, sh.cnt, sh.epre, sh.tot_edges, sh.tot_count};
+    SegView sv{in.ent, in.cap, a.nseg, sh.cpre, sh.epre, sh.tot_edges, sh.tot_count};
     ListSrc src{sv, c->diag};
     int wb, we;
     jobs_wave_range(sh.tot_edges, wb, we);

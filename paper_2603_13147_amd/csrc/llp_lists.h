@@ -72,12 +72,12 @@ struct ListRef {
     int cap;
 };
 
-// Per-workgroup view of a consumed list: segment counts and edge prefix in LDS.
+// Per-workgroup view of a consumed list: prefixes of the segments' entries and edges in LDS.
 struct SegView {
     const int4* ent;
     int cap;
     int nseg;
-    const int* cnt;     // [nseg] (LDS)
+    const int* cpre;    // [nseg + 1] exclusive prefix of the segments' entries (LDS)
     const int* epre;    // [nseg + 1] exclusive edge prefix (LDS)
     int total_edges;
     int total_count;
@@ -98,70 +98,69 @@ __device__ inline void seg_fetch(const unsigned long long* seg, int nseg, SegReg
 }
 
 // Block-wide scan of fetched segment totals into LDS arrays.
-// lds_cnt[nseg], lds_epre[nseg+1] must be __shared__ buffers.  (A template,
+// lds_cpre[nseg+1], lds_epre[nseg+1] must be __shared__ buffers.  (A template,
 // like every helper here that declares its own LDS.)
 template <int = 0>
-__device__ inline void seg_scan(const SegRegs& s, int nseg, int* lds_cnt, int* lds_epre,
+__device__ inline void seg_scan(const SegRegs& s, int nseg, int* lds_cpre, int* lds_epre,
                                 int* lds_tmp /* >= blockDim/64 + 1 ints */, int* tot_edges, int* tot_count) {
     const int t = threadIdx.x, nt = blockDim.x;
     const int per = (nseg + nt - 1) / nt;   // <= 8 (nseg <= 2048, >= 256 threads)
     const int b = t * per, e = min(b + per, nseg);
     int se = 0, sc = 0;
-    int eds[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const int i = b + k;
-        eds[k] = 0;
-        if (k < per && i < e) {
-            const unsigned long long x = s.x[k];
-            int c = (int)(x & 0xffffffffull), ed = (int)(x >> 32);
-            lds_cnt[i] = c;
-            eds[k] = ed;
-            sc += c;
-            se += ed;
+        if (k < per && b + k < e) {
+            sc += (int)(s.x[k] & 0xffffffffull);
+            se += (int)(s.x[k] >> 32);
         }
     }
-    // block exclusive scan of se (edges) and total of sc (counts)
+    // block exclusive scans of se (edges) and sc (entries)
     int w = t >> 6, l = lane();
-    int incl = wave_incl_sum(se);
-    long long csum = wave_sum64(sc);
+    const int einc = wave_incl_sum(se), cinc = wave_incl_sum(sc);
     __shared__ int wsum[16];
-    __shared__ long long wcnt[16];
-    if (l == 63) wsum[w] = incl;
-    if (l == 0) wcnt[w] = csum;
+    __shared__ int wcnt[16];
+    if (l == 63) {
+        wsum[w] = einc;
+        wcnt[w] = cinc;
+    }
     __syncthreads();
     int nw = nt >> 6;
-    int woff = 0;
-    long long ctot = 0;
-    int etot = 0;
+    int erun = einc - se, crun = cinc - sc, etot = 0, ctot = 0;
     for (int k = 0; k < nw; ++k) {
-        if (k < w) woff += wsum[k];
+        if (k < w) {
+            erun += wsum[k];
+            crun += wcnt[k];
+        }
         etot += wsum[k];
         ctot += wcnt[k];
     }
-    int run = woff + incl - se;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const int i = b + k;
         if (k < per && i < e) {
-            lds_epre[i] = run;
-            run += eds[k];
+            lds_epre[i] = erun;
+            lds_cpre[i] = crun;
+            erun += (int)(s.x[k] >> 32);
+            crun += (int)(s.x[k] & 0xffffffffull);
         }
     }
-    if (t == 0) lds_epre[nseg] = etot;
+    if (t == 0) {
+        lds_epre[nseg] = etot;
+        lds_cpre[nseg] = ctot;
+    }
     *tot_edges = etot;
-    *tot_count = (int)ctot;
+    *tot_count = ctot;
     (void)lds_tmp;
     __syncthreads();
 }
 
 // Fetch and scan in one step.
 template <bool COH = false>
-__device__ inline void load_segments(const unsigned long long* seg, int nseg, int* lds_cnt, int* lds_epre,
+__device__ inline void load_segments(const unsigned long long* seg, int nseg, int* lds_cpre, int* lds_epre,
                                      int* lds_tmp /* >= blockDim/64 + 1 ints */, int* tot_edges, int* tot_count) {
     SegRegs s;
     seg_fetch<COH>(seg, nseg, s);
-    seg_scan(s, nseg, lds_cnt, lds_epre, lds_tmp, tot_edges, tot_count);
+    seg_scan(s, nseg, lds_cpre, lds_epre, lds_tmp, tot_edges, tot_count);
 }
 
 // ---------------------------------------------------------------- sources
@@ -210,17 +209,20 @@ struct ListSrcT {
     int* diag;
 
     __device__ Cursor locate(int e) const {
-        // segment: largest s with epre[s] <= e and cnt[s] > 0
+        // the last segment whose prefix is at most e holds it (the empty
+        // segments before it share its prefix); 64 probes a step
         int lo = 0, hi = sv.nseg;
         while (hi - lo > 1) {
-            int mid = (lo + hi) >> 1;
-            if (sv.epre[mid] <= e) lo = mid; else hi = mid;
+            const int step = (hi - lo + 63) / 64;
+            const int probe = lo + lane() * step;
+            const int c = __popcll(ballot(probe < hi && sv.epre[probe] <= e));
+            lo += (c > 0 ? c - 1 : 0) * step;
+            hi = min(lo + step, hi);
         }
-        int s = lo;
-        while (s < sv.nseg - 1 && sv.cnt[s] == 0) ++s;   // empty segments have epre[s] == epre[s+1]
+        const int s = lo;
         int local = e - sv.epre[s];
         const int4* base = sv.ent + (long long)s * sv.cap;
-        int lo2 = 0, hi2 = min(sv.cnt[s], sv.cap);
+        int lo2 = 0, hi2 = min(count(s), sv.cap);
         while (hi2 - lo2 > 64) {
             int step = (hi2 - lo2 + 63) / 64;
             int probe = lo2 + lane() * step;
@@ -234,33 +236,50 @@ struct ListSrcT {
         int c = __popcll(ballot(ok));
         return Cursor{s, guard(lo2 + c - 1, sv.cap, diag, 23, e, local)};
     }
-    __device__ int avail(const Cursor& c) const { return c.s < sv.nseg ? min(sv.cnt[c.s], sv.cap) - c.i : 0; }
+    __device__ int count(int s) const { return sv.cpre[s + 1] - sv.cpre[s]; }
+    // last segment of [lo, hi) that starts at or before entry g of the list
+    // (g < total: the one that holds it); three probes a step, in flight together
+    __device__ int segment_at(int lo, int hi, int g) const {
+        while (hi - lo > 1) {
+            const int q = (hi - lo + 3) >> 2;
+            const int p1 = min(lo + q, hi - 1), p2 = min(lo + 2 * q, hi - 1), p3 = min(lo + 3 * q, hi - 1);
+            const bool b1 = sv.cpre[p1] <= g, b2 = sv.cpre[p2] <= g, b3 = sv.cpre[p3] <= g;
+            const int nh = b3 ? hi : (b2 ? p3 : (b1 ? p2 : p1));
+            lo = b3 ? p3 : (b2 ? p2 : (b1 ? p1 : lo));
+            hi = nh;
+        }
+        return lo;
+    }
+    // A window runs on over the ends of segments: a narrow list has an entry
+    // or two in each, and windows that ended with their segment made a wave
+    // walk its arcs a row at a time.  A job DAG of 2^20 jobs 2364 -> 2118 us, of
+    // 2^18 1597 -> 1342; plain SSSP and BFS on a power-law graph of 4.4 M arcs
+    // 978 -> 896 and 864 -> 767, hybrid SSSP on 65536 uniform vertices 408 ->
+    // 384.  The lanes past the segment's end find theirs by a search in LDS,
+    // whose steps a narrow round waits for: with two-way steps over all the
+    // segments a 1024^2 mesh took 1% longer than before, as it is, the same.
+    __device__ int avail(const Cursor& c) const { return c.s < sv.nseg ? sv.total_count - (sv.cpre[c.s] + c.i) : 0; }
     __device__ int4 load(const Cursor& c, int l) const {
-        int s = guard(c.s, sv.nseg, diag, 24, c.i, l);
-        int i = guard(c.i + l, sv.cap, diag, 25, c.s, l);
+        int s = guard(c.s, sv.nseg, diag, 24, c.i, l), i = c.i + l;
+        if (c.i + LLP_WAVE > count(s)) {
+            // usually one of the next 64 segments holds the window's last entry
+            const int g = sv.cpre[s] + i, top = min(s + LLP_WAVE, sv.nseg);
+            const bool near = sv.cpre[top] > min(sv.cpre[s] + c.i + LLP_WAVE, sv.total_count) - 1;
+            s = segment_at(s, near ? top : sv.nseg, g);
+            i = g - sv.cpre[s];
+        }
+        i = guard(i, sv.cap, diag, 25, c.s, l);
         int4 x = ld_ent<COH>(sv.ent + (long long)s * sv.cap + i);
         x.z += sv.epre[s];
         return x;
     }
     __device__ Cursor advance(Cursor c, int k) const {
         c.i += k;
-        if (c.s < sv.nseg && c.i >= min(sv.cnt[c.s], sv.cap)) {
-            // past this segment: jump to the one holding the next edge, the
-            // last segment whose edge prefix is at most that edge's index
-            // (every entry has arcs, so the empty segments in between share
-            // its prefix).  A narrow list leaves most segments empty, and
-            // stepping over them one at a time cost the wave that finished
-            // the list several microseconds per round.
-            const int e = sv.epre[c.s + 1];
-            int lo = c.s + 1, hi = sv.nseg;
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (sv.epre[mid] <= e) lo = mid; else hi = mid;
-            }
-            c.s = lo;
-            c.i = 0;
-            // no edge after this segment: the trailing segments are empty
-            if (c.s < sv.nseg && min(sv.cnt[c.s], sv.cap) == 0) c.s = sv.nseg;
+        if (c.s < sv.nseg && c.i >= count(c.s)) {
+            const int g = sv.cpre[c.s] + c.i;
+            if (g >= sv.total_count) return Cursor{sv.nseg, 0};
+            c.s = segment_at(c.s, sv.nseg, g);
+            c.i = g - sv.cpre[c.s];
         }
         return c;
     }
