@@ -430,12 +430,16 @@ struct JobsLayout {
     int cap;
 };
 
-static JobsLayout jobs_layout(int64_t n, int64_t E) {
+// One list segment (and workgroup) per CU: a level is a chain of round trips,
+// and half the workgroups of two per CU scan half the totals and end sooner.
+// At 2^20, 2^18, 2^16 and 10^4 jobs on 256 CUs: one per CU 2117, 1326, 944 and
+// 602 us, two 2125, 1345, 1004 and 616, three 2152, 1421, 1065 and 637 (while a
+// window of entries ended with its segment two were the better: 2.57 ms
+// against 2.61).  The scratch asked for is that of two, which is never smaller.
+constexpr int JOBS_PER_CU = 1, JOBS_SCRATCH_PER_CU = 2;
+static JobsLayout jobs_layout(int64_t n, int64_t E, int per_cu) {
     JobsLayout L;
-    // two segments per CU: the narrow levels run in one workgroup whatever the
-    // count, and the wide ones spread over more workgroups (at 2^20 jobs on 256
-    // CUs: 512 segments 2.57 ms, 256 2.61 ms, 128 2.81 ms, 64 3.46 ms)
-    L.nseg = device_info().cus * 2;
+    L.nseg = device_info().cus * per_cu;
     if (L.nseg > J_MAX_SEG) L.nseg = J_MAX_SEG;
     if (L.nseg < 1) L.nseg = 1;
     long long W = (long long)L.nseg * JW;
@@ -446,8 +450,8 @@ static JobsLayout jobs_layout(int64_t n, int64_t E) {
     return L;
 }
 
-static size_t jobs_ws(int64_t n, int64_t E, JArgs* a, char* base, size_t cap) {
-    JobsLayout L = jobs_layout(n, E);
+static size_t jobs_ws(int64_t n, int64_t E, int per_cu, JArgs* a, char* base, size_t cap) {
+    JobsLayout L = jobs_layout(n, E, per_cu);
     Carver cv{base, cap, 0, base == nullptr};
     int* cnt = cv.take<int>(n);
     JCtrl* ctrl = cv.take<JCtrl>(1);
@@ -476,7 +480,7 @@ static size_t jobs_ws(int64_t n, int64_t E, JArgs* a, char* base, size_t cap) {
 size_t graph_workspace_bytes(int64_t n, int64_t m, int chunk);
 
 size_t jobs_workspace_bytes(int64_t n, int64_t E, int chunk) {
-    size_t a = jobs_ws(n, E, nullptr, nullptr, 0);
+    size_t a = jobs_ws(n, E, JOBS_SCRATCH_PER_CU, nullptr, nullptr, 0);
     size_t b = graph_workspace_bytes(n, E, chunk);
     return a > b ? a : b;
 }
@@ -527,11 +531,11 @@ int solve_jobs(int32_t n, const int32_t* pred_ptr, const int32_t* pred_idx, cons
     a.S = start;
     a.narrow = o.chunk < 0 ? 0 : (o.chunk == 0 ? JN_ARCS : std::min<int>(o.chunk, JN_ARCS));
     a.max_rounds = o.max_rounds > 0 ? o.max_rounds : (int64_t)n + 2;
-    size_t need = jobs_ws(n, E, nullptr, nullptr, 0);
+    size_t need = jobs_ws(n, E, JOBS_SCRATCH_PER_CU, nullptr, nullptr, 0);
     void* ws = nullptr;
     s = get_workspace(o, need, &ws);
     if (s) return s;
-    jobs_ws(n, E, &a, (char*)ws, need);
+    jobs_ws(n, E, JOBS_PER_CU, &a, (char*)ws, need);
 
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timing = (o.flags & LLP_TIMING) && o.stats;
