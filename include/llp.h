@@ -143,7 +143,7 @@ typedef struct {
     volatile int32_t* abort_host; /* [host, pinned] optional: a nonzero value aborts at the next round */
     llp_stats* stats;           /* [host] optional */
     int32_t chunk;              /* launch knob, 0 = default: graph sweeps: workgroups (list segments) per CU
-                                   (default 2, SSSP and BFS of fewer than 2^20 arcs 1; at most 8; pass
+                                   (default 2, SSSP and BFS of fewer than 2^21 arcs 1; at most 8; pass
                                    the same opts to llp_workspace_bytes);
                                    stable marriage: proposals per thread per launch; batch: instances per
                                    queue claim; jobs readiness: widest level, in arcs, run by one

@@ -1025,7 +1025,8 @@ __device__ __forceinline__ bool carry_step(const GArgs& a, const EdgeCtx& c, int
 // stamped rows the way a dense round does, each row by one wave that is its
 // only writer.  That reads every row's bounds and stamp, and splits the rows
 // evenly by arcs only as far as the stamped ones are spread evenly, hence the
-// two limits.  Plain SSSP on a power-law graph of 4.4 M arcs: 1270 -> 959 us
+// two limits.  Plain SSSP on a power-law graph of 4.4 M arcs: 1270 -> 959 us,
+// 866 with windows that run over segments
 // (expansion of its widest rounds 80 -> 30, evaluation 100 -> 55), of 18 M
 // 2720 -> 2050, of 71 M 10.2 -> 7.9 ms, plain BFS on 18 M 2200 -> 1690.  Limits
 // of 2^13 to 2^16 arcs and n / 32 to n / 8 measure alike (965 to 980 on the
@@ -1759,12 +1760,14 @@ struct GraphLayout {
 static int graph_wgs_per_cu(int chunk) { return chunk > 0 ? (chunk > 8 ? 8 : chunk) : 2; }
 // A graph of fewer arcs than this runs one workgroup per CU where the library
 // chooses: its rounds are short, and a launch of half the workgroups scans half
-// the list segments and ends sooner.  Hybrid and plain, SSSP and BFS, one per CU
-// against two: power-law graphs of 0.28 M arcs 192 / 457 / 140 / 395 us against
-// 197 / 501 / 149 / 428, of 0.56 M 211 / 504 / 142 / 421 against 219 / 548 / 150 /
-// 451, a mesh of 0.36 M 0.95 and 3.7 ms against 0.97 and 4.4; of 1.1 M arcs 234 /
-// 618 / 154 / 537 against 230 / 643 / 160 / 561, of 4.5 M 330 / 1017 against 318 / 985.
-constexpr int64_t GRAPH_NARROW_M = 1 << 20;
+// the list segments and ends sooner.  Hybrid and plain, SSSP and BFS in us, one
+// per CU against two: power-law graphs of 0.28 M arcs 187 / 419 / 143 / 366
+// against 195 / 446 / 153 / 383, of 1.1 M 235 / 572 / 159 / 480 against 236 /
+// 577 / 166 / 489, of 2.2 M 281 / 715 / 194 / 617 against 285 / 690 / 193 / 579, of
+// 4.5 M 330 / 977 / 219 / 849 against 318 / 903 / 225 / 768; hybrid SSSP and BFS on
+// meshes of 0.36 M arcs 954 and 3776 against 987 and 4918, of 2.0 M 2709 and
+// 9895 against 2768 and 11786.
+constexpr int64_t GRAPH_NARROW_M = 1 << 21;
 // workgroups per CU the autotuner tries (llp_autotune_graph); a solve that
 // leaves the choice to the library (chunk 0) takes the record of its size
 // class, so workspaces sized for chunk 0 hold every candidate

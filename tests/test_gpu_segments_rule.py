@@ -1,4 +1,4 @@
-"""The library's own choice of list segments (one workgroup per CU below 2^20
+"""The library's own choice of list segments (one workgroup per CU below 2^21
 arcs, two from there on): either side of the limit against the oracle, in the
 scratch the size query states and with every explicit choice beside it."""
 import numpy as np
@@ -13,7 +13,7 @@ torch = pytest.importorskip("torch")
 llp = pytest.importorskip("paper_2603_13147_amd")
 
 
-@pytest.mark.parametrize("m", [(1 << 20) - 1, 1 << 20])
+@pytest.mark.parametrize("m", [(1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21])
 @pytest.mark.parametrize("bfs", [False, True])
 def test_limit(m, bfs):
     n = 30000
