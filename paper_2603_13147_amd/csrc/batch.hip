@@ -105,7 +105,7 @@ template <int CH>
 __global__ void __launch_bounds__(ch_max_block(CH), CH <= 16 ? 8 : 1) k_batch(BArgs a) {
     extern __shared__ __align__(8) int lds[];
     __shared__ int claim;
-    __shared__ int sfl[6];
+    __shared__ int sfl[SW_FLAGS];
     for (;;) {
         if (threadIdx.x == 0) claim = atomicAdd(&a.ctrl->head, a.chunk);
         __syncthreads();

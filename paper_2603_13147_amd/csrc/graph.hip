@@ -1743,7 +1743,7 @@ __global__ void __launch_bounds__(SMALL_T) k_graph_small(int n, int m, const int
                                                          const int* out_w, int source, int* dist, long long max_rounds,
                                                          int* status) {
     __shared__ unsigned long long lds[(sssp_wg_words(SMALL_N, SMALL_T, SMALL_PER) + 1) / 2];
-    __shared__ int fl[6];
+    __shared__ int fl[SW_FLAGS];
     const int st = sssp_wg<SMALL_PER, UNIT, false>(out_ptr, out_dst, out_w, n, m, source, sssp_wg_carve<SMALL_PER>(lds, n),
                                                    fl, dist, max_rounds);
     if (threadIdx.x == 0) *status = st;

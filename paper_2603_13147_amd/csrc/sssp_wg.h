@@ -31,6 +31,11 @@
 namespace llp {
 
 constexpr int SW_LONG = 256;    // longest row taken through the table
+// Flags: something was taken, and bad input was met, each by round modulo 3 (a
+// wave past a round's only barrier may set the next round's before another has
+// read this one's; the words it reads are cleared no sooner than two rounds
+// on, so all waves leave by the same round); an arc overflowed; a distance did.
+constexpr int SW_TAKEN = 0, SW_BAD = 3, SW_OVF_ARC = 6, SW_OVF = 7, SW_FLAGS = 8;
 
 // LDS words needed for n vertices and T threads, n + 1 row offsets among them.
 // per: arc positions per lane and step, a multiple of 4.
@@ -90,7 +95,7 @@ __device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, co
 }
 
 // Solves with the calling workgroup.  gptr[n + 1], dst[m],
-// wgt[m]: out-CSR; dist[n]: the output (INF = unreached).  fl: LDS int[6].
+// wgt[m]: out-CSR; dist[n]: the output (INF = unreached).  fl: LDS int[SW_FLAGS].
 // Returns the status, uniform in the workgroup.
 template <int PER, bool UNIT, bool NEG>
 __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src,
@@ -101,13 +106,14 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
     for (int v = t; v < n; v += T) s.G[v] = v == src ? LLP_INF : 0;
     for (int v = t; v <= n; v += T) s.ptr[v] = gptr[v];
     for (int i = t; i < nb; i += T) s.act[i] = i == (src >> 6) ? 1ull << (src & 63) : 0ull;
-    if (t < 6) fl[t] = 0;   // fl[0 .. 2]: something was taken, by round modulo 3; fl[3]: bad input; fl[4]: overflow
+    if (t < SW_FLAGS) fl[t] = 0;
     __syncthreads();
     long long r = 0;
     bool more = true;
+    int st = LLP_OK;
     for (; more && r < max_rounds; ++r) {
         bool bad = false, ovf = false, did = false;
-        if (t == 0) fl[(r + 1) % 3] = 0;   // last read in round r - 2
+        if (t == 0) fl[SW_TAKEN + (r + 1) % 3] = fl[SW_BAD + (r + 1) % 3] = 0;   // last read in round r - 2
         for (int c = wave; c < nb; c += nw * LLP_WAVE) {   // lane l looks at block c + nw l
             uint64_t todo = ballot(c + nw * l < nb && s.act[min(c + nw * l, nb - 1)] != 0ull);
             for (; todo; todo &= todo - 1) {
@@ -189,26 +195,26 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
                 }
             }
         }
-        if (did && l == 0) fl[r % 3] = 1;
-        if (bad) fl[3] = 1;
-        if (ovf) fl[4] = 1;
+        if (did && l == 0) fl[SW_TAKEN + r % 3] = 1;
+        if (bad) fl[SW_BAD + r % 3] = 1;
+        if (ovf) fl[SW_OVF_ARC] = 1;
         __syncthreads();
-        more = fl[r % 3] != 0 && fl[3] == 0;
+        if (fl[SW_BAD + r % 3]) st = LLP_E_INPUT;
+        more = fl[SW_TAKEN + r % 3] != 0 && st == LLP_OK;
     }
-    int st = LLP_OK;
-    if (fl[3]) st = LLP_E_INPUT;
-    else if (more) st = LLP_E_NOT_CONVERGED;
-    // overflow: an unreached vertex with a reached in-neighbour
-    if (st == LLP_OK && fl[4]) {
+    if (more) st = LLP_E_NOT_CONVERGED;
+    // overflow: an unreached vertex with a reached in-neighbour (every wave has
+    // left the rounds: none sets the flag any more)
+    if (st == LLP_OK && fl[SW_OVF_ARC]) {
         for (int u = t; u < n; u += T) {
             if (s.G[u] <= 0) continue;
             for (int k = max(s.ptr[u], 0); k < min(s.ptr[u + 1], m); ++k) {
                 const int x = dst[k];
-                if ((unsigned)x < (unsigned)n && s.G[x] == 0) fl[5] = 1;
+                if ((unsigned)x < (unsigned)n && s.G[x] == 0) fl[SW_OVF] = 1;
             }
         }
         __syncthreads();
-        if (fl[5]) st = LLP_E_OVERFLOW;
+        if (fl[SW_OVF]) st = LLP_E_OVERFLOW;
     }
     for (int v = t; v < n; v += T) {
         const int g = s.G[v];

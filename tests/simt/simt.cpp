@@ -5,7 +5,9 @@
 // launch keeps every workgroup live and switches between them whenever all
 // of a workgroup's threads wait (at a wave operation, a barrier, or a
 // __builtin_amdgcn_s_sleep, which yields), each workgroup with its own copy
-// of the __shared__ variables (poison-filled when it starts).
+// of the __shared__ variables (poison-filled when it starts).  With SIMT_LAG set
+// one wave of the workgroup, another each time, stays behind at every barrier
+// until the others can go no further.
 #include <sys/mman.h>
 #include <unistd.h>
 
@@ -53,7 +55,7 @@ simt_switch:
 
 namespace simt {
 
-enum State { RUN = 0, AT_WAVE = 1, AT_BAR = 2, DONE = 3, YIELD = 4 };
+enum State { RUN = 0, AT_WAVE = 1, AT_BAR = 2, DONE = 3, YIELD = 4, HELD = 5 };
 
 struct Fiber {
     void* sp;
@@ -270,11 +272,19 @@ static bool release(Fiber* F, int nf) {
         }
     }
     if (live && atb == live && same) {
+        static const bool lag = getenv("SIMT_LAG") != nullptr;
+        static unsigned turn = 0;
+        const int late = lag ? (int)(turn++ % (unsigned)nw) : -1;
         for (int i = 0; i < nf; ++i)
-            if (F[i].state == AT_BAR) F[i].state = RUN;
+            if (F[i].state == AT_BAR) F[i].state = F[i].wave == late ? HELD : RUN;
         return true;
     }
-    return false;
+    for (int i = 0; i < nf; ++i)
+        if (F[i].state == HELD) {
+            F[i].state = RUN;
+            prog = true;
+        }
+    return prog;
 }
 
 // Run a workgroup's threads until every one has finished or waits.  Returns
