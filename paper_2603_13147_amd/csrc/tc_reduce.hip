@@ -82,8 +82,9 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
                                                       const int* __restrict__ dst, unsigned* __restrict__ bits,
                                                       TCtrl* ctl) {
     extern __shared__ unsigned long long tl[];
-    __shared__ int any[3];
-    __shared__ int bad;
+    // by round modulo 3: a vertex was taken; bad input was met (a wave past the
+    // round's barrier may set the next round's before another has read this one's)
+    __shared__ int any[3], bad[3];
     const int t = threadIdx.x, l = lane();
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int nb = (n + 63) >> 6, T = blockDim.x, nw = T >> 6;   // nb <= 64 nw
@@ -100,13 +101,13 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
     }
     const int rw = BITS == 32 ? n : (n + 1) >> 1;
     for (int i = t; i < rw; i += T) R[i] = 0u;
-    if (t < 3) any[t] = 0;
-    if (t == 0) bad = 0;
+    if (t < 3) any[t] = bad[t] = 0;
     __syncthreads();
     int r = 0;
+    bool failed = false;
     for (;; ++r) {
         bool b2 = false, did = false;
-        if (t == 0) any[(r + 1) % 3] = 0;   // last read in round r - 2
+        if (t == 0) any[(r + 1) % 3] = bad[(r + 1) % 3] = 0;   // last read in round r - 2
         const int mine = wave + nw * l;
         uint64_t todo = ballot(mine < nb && tl[min(mine, nb - 1)] != 0ull);
         int blk = 0, pb = 0, pe = 0;   // the block to take, its rows' offsets on the way
@@ -177,9 +178,10 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
             }
         }
         if (did && l == 0) any[r % 3] = 1;
-        if (b2) bad = 1;
+        if (b2) bad[r % 3] = 1;
         __syncthreads();
-        if (!any[r % 3] || bad) break;
+        failed = bad[r % 3] != 0;
+        if (!any[r % 3] || failed) break;
     }
     // transpose: 64 columns per step, the words of row u0 + s in lane s
     const int words = (n + 31) >> 5;
@@ -199,7 +201,7 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
         }
     }
     if (t == 0) {
-        if (bad) {
+        if (failed) {
             set_status(&ctl->status, LLP_E_INPUT);
             record_diag(ctl->diag, 81, u0, n, 0, 0);
         }

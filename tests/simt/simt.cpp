@@ -7,7 +7,8 @@
 // __builtin_amdgcn_s_sleep, which yields), each workgroup with its own copy
 // of the __shared__ variables (poison-filled when it starts).  With SIMT_LAG set
 // one wave of the workgroup, another each time, stays behind at every barrier
-// until the others can go no further.
+// until the others can go no further, and a barrier that a wave has ended
+// before is an error.
 #include <sys/mman.h>
 #include <unistd.h>
 
@@ -275,6 +276,10 @@ static bool release(Fiber* F, int nf) {
         static const bool lag = getenv("SIMT_LAG") != nullptr;
         static unsigned turn = 0;
         const int late = lag ? (int)(turn++ % (unsigned)nw) : -1;
+        if (lag && live != nf) {
+            cur = &F[0];
+            die("a barrier that ended waves no longer reach");
+        }
         for (int i = 0; i < nf; ++i)
             if (F[i].state == AT_BAR) F[i].state = F[i].wave == late ? HELD : RUN;
         return true;

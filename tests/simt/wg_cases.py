@@ -93,5 +93,25 @@ def batches():
                     "equal": all(np.array_equal(d, w) for d, w in zip(dist, want) if w is not None)}), flush=True)
 
 
+def closures():
+    """Well-formed graphs against the oracle, then the same with one id or
+    offset out of range in a row that only later rounds reach."""
+    for n, deg, seed in ((700, 2, 0), (1100, 3, 1), (1500, 2, 2)):
+        g = llpgen.uniform_graph(n, deg * n, seed=seed)
+        far = oracle.bfs(n, g.src, g.dst, 0)
+        order = np.argsort(far)
+        for what, value in ((None, 0), ("head", n), ("head", -1), ("end", 1 << 30)):
+            for late in order[[n // 2, n - 1]] if what else order[:1]:
+                ptr, dst, _ = spoiled(g, int(late), what, value) if what else spoiled(g, 0, "weight", 1)
+                words = (n + 31) // 32
+                bits = dev(np.zeros(n * words, np.uint32))
+                code = L.llp_solve_tc(n, len(dst), dev(ptr), dev(dst), bits, ctypes.byref(opts()))
+                row = {"case": f"{n}-{what}", "code": code}
+                if not what:
+                    want = oracle.transitive_closure(n, g.src, g.dst)
+                    row["equal"] = bool(np.array_equal(host(bits, n * words, np.uint32).reshape(n, words), want))
+                print(json.dumps(row), flush=True)
+
+
 if __name__ == "__main__":
-    {"batch": batches}[sys.argv[1]]()
+    {"batch": batches, "closure": closures}[sys.argv[1]]()

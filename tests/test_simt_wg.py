@@ -31,3 +31,10 @@ def test_batch_instances_after_a_malformed_one():
     for x in rows:
         assert x["code"] == 2, x                      # LLP_E_INPUT: the first nonzero instance status
         assert x["bad"] == [2, 2, 2] and x["good"] == [0, 0, 0] and x["equal"], x
+
+
+def test_closures_well_formed_and_not():
+    rows = run("closure")
+    assert len(rows) == 3 * 7
+    for x in rows:
+        assert x["code"] == 0 and x["equal"] if x["case"].endswith("None") else x["code"] == 2, x
