@@ -21,7 +21,7 @@ extern "C" size_t llp_workspace_bytes(int kind, int64_t n, int64_t m, const llp_
         case LLP_KIND_JOBS:
             return llp::jobs_workspace_bytes(n, m, chunk);
         case LLP_KIND_KNAPSACK:
-            return n < 0 || m < 0 ? llp::KN_HEADER_BYTES : llp::knap_bytes(llp::knap_groups(n, m), m);
+            return llp::knap_workspace_bytes(n, m);
         case LLP_KIND_TC:
             return llp::tc_workspace_bytes(n);
         case LLP_KIND_REDUCE:

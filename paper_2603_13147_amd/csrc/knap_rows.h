@@ -34,7 +34,6 @@
 
 namespace llp {
 
-constexpr int KN_MAX_W = 16383;
 constexpr int KN_MAX_CH = 32;      // cells per thread at most
 
 // Largest workgroup a kernel holding up to ch row cells per thread in

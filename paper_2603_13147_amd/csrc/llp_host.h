@@ -73,6 +73,7 @@ void* pinned_scratch(size_t bytes);
 // Workspace of a knapsack (knapsack.hip): a header, then the rows of the groups
 // the items are split into and of their merges (2 KN_GROUPS rows at most).
 // A workspace of the header alone is enough for a solve that is not split.
+constexpr int KN_MAX_W = 16383;
 constexpr size_t KN_HEADER_BYTES = 256;
 constexpr int KN_GROUPS = 32;
 inline size_t knap_stride(int64_t W) { return ((size_t)W + 4) & ~(size_t)3; }   // words per row
@@ -99,6 +100,11 @@ inline int knap_groups(int64_t items, int64_t W) {
 }
 inline size_t knap_bytes(int groups, int64_t W) {
     return KN_HEADER_BYTES + (groups > 1 ? (size_t)2 * groups * knap_stride(W) * 4 : 0);
+}
+// What a solve of these sizes can use; the header for sizes that it refuses.
+inline size_t knap_workspace_bytes(int64_t items, int64_t W) {
+    if (items < 0 || items > INT32_MAX || W < 0 || W > KN_MAX_W) return KN_HEADER_BYTES;
+    return knap_bytes(knap_groups(items, W), W);
 }
 
 // Wait for the stream and read `bytes` from device pointer src into dst via the
