@@ -24,3 +24,15 @@ def size(items, W):
 def test_sizes_no_solve_accepts_ask_for_the_header(items, W):
     """So a binding that sizes first still gets the solver's argument error, not an allocation of gigabytes."""
     assert size(items, W) == HEADER
+
+
+@pytest.mark.parametrize("items,W", [(110, 3), (150, 40), (100, 255), (257, 511), (257, 512), (300, 513), (1000, 767),
+                                     (1000, 1024), (401, 4097), (999, 16383), (2000, 1500), (1500, 1500)])
+def test_sizes_of_the_split_tests_split(items, W):
+    """The GPU tests of the split have these sizes; a rule that kept them whole would empty those tests."""
+    assert size(items, W) > HEADER
+
+
+@pytest.mark.parametrize("items,W", [(0, 0), (1, 16383), (33, 40), (64, 256)])
+def test_small_knapsacks_stay_whole(items, W):
+    assert size(items, W) == HEADER
