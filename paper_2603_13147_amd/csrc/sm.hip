@@ -230,13 +230,19 @@ __global__ void k_sm_chain(SArgs a, int r) {
 // women's best keys and the men's positions live in LDS, so the displacement
 // atomic and the reads of the keys stay on the CU (across XCDs an atomic must
 // reach the memory side).  See k_sm_lds.
-constexpr int SM_LDS_MAX = 12288;   // 8 B of LDS per man: 96 KB
+constexpr int SM_LDS_MAX = 12288;   // 10 B of LDS per man: 120 KB
 constexpr int SM_COMBO = 64;        // list positions per man held as (woman, rank) pairs
 constexpr int SM_LDS_LOOKAHEAD = 6;   // women examined per round trip of a thread's chain in k_sm_lds
 constexpr unsigned SM_FREE = ~0u;   // key of a woman nobody holds
 constexpr int SM_MAN_BITS = 14;     // a key is rank << 14 | man (n <= SM_LDS_MAX < 2^14)
 constexpr int SM_MAN = (1 << SM_MAN_BITS) - 1;
-constexpr int SM_HOPS = 16;         // steps of a thread's chain before its man is parked
+constexpr int SM_HOPS = 16;         // steps of a thread's chain in the first pass
+// The passes after it (see k_sm_lds):
+constexpr int SM_MANY = 128;        // chains from which a pass may go by threads
+constexpr int SM_TRIES = 128;       // positions tried per man displaced below which it does
+constexpr int SM_PASS_HOPS = 64;    // and its steps per chain
+constexpr int SM_FEW = 64;          // chains up to which a wave runs each to its end
+constexpr int SM_WAVE_HOPS = 16;    // men a wave's chain displaces per pass while there are more
 constexpr int SM_LDS_THREADS = 1024;
 
 // The i-th woman w on m's list and her rank of m, as w | rank << 16.
@@ -260,147 +266,232 @@ __global__ void k_sm_combo(SArgs a) {
     a.combo[(long long)m * SM_COMBO + i] = sm_pair(a, m, i);
 }
 
+// Adds the wave's x and y to words in LDS.
+__device__ __forceinline__ void sm_add(int* px, int x, int* py, int y) {
+    const int sx = (int)wave_sum64(x), sy = (int)wave_sum64(y);
+    if (lane() == 0) {
+        atomicAdd(px, sx);
+        atomicAdd(py, sy);
+    }
+}
+
+// Up to `hops` steps of a thread's chain from man m at position g on, while g
+// is below the table's end (PAST: the list's).  Returns whether the chain is
+// unfinished: m then stands at g.  tries, moves: positions tried, men displaced.
+template <bool PAST>
+__device__ __forceinline__ bool sm_thread_chain(const SArgs& a, unsigned* best, unsigned short* nx, int hops, int& m, int& g,
+                                                int& tries, int& moves) {
+    const int k = min(a.n, SM_COMBO), end = PAST ? a.n : k;
+    for (int hop = 0; hop < hops && g < end; ++hop) {
+        // positions past the end read the last entry, whose woman is then
+        // taken only at her own position
+        int cw[SM_LDS_LOOKAHEAD];
+        unsigned bv[SM_LDS_LOOKAHEAD];
+        if (!PAST || g + SM_LDS_LOOKAHEAD <= k) {
+#pragma unroll
+            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) cw[i] = a.combo[m * SM_COMBO + min(g + i, k - 1)];
+        } else {
+#pragma unroll
+            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) cw[i] = sm_pair(a, m, min(g + i, end - 1));
+        }
+#pragma unroll
+        for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) bv[i] = best[cw[i] & 0xffff];
+        int at = -1, w = 0;
+        unsigned key = 0;
+#pragma unroll
+        for (int i = SM_LDS_LOOKAHEAD - 1; i >= 0; --i) {
+            const unsigned ki = ((unsigned)cw[i] >> 16 << SM_MAN_BITS) | (unsigned)m;
+            if (g + i < end && ki < bv[i]) {
+                at = g + i;
+                w = cw[i] & 0xffff;
+                key = ki;
+            }
+        }
+        if (at < 0) {
+            tries += min(SM_LDS_LOOKAHEAD, end - g);
+            g = min(g + SM_LDS_LOOKAHEAD, end);
+            continue;
+        }
+        tries += at + 1 - g;
+        nx[m] = (unsigned short)(at + 1);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        const unsigned old = atomicMin(&best[w], key);
+        if (old == SM_FREE) return false;
+        if (old > key) {
+            ++moves;
+            m = (int)(old & SM_MAN);
+            g = nx[m];
+        } else {
+            g = at + 1;
+        }
+    }
+    return true;
+}
+
+// Up to `hops` displacements of a wave's chain (m and g uniform in the wave).
+// Returns whether the chain is unfinished: m then stands at g.  bad is set
+// where a man exhausts his list.
+template <bool LIMIT>
+__device__ __forceinline__ bool sm_wave_chain(const SArgs& a, unsigned* best, unsigned short* nx, int* bad, int hops, int& m,
+                                              int& g, int& tries, int& moves) {
+    const int n = a.n, k = min(n, SM_COMBO), l = lane();
+    int row = l < k ? a.combo[m * SM_COMBO + l] : 0;
+    for (int hop = 0; !LIMIT || hop < hops;) {
+        // the first of m's women from position g on who prefers him
+        int at = -1, w = row & 0xffff;
+        unsigned key = ((unsigned)row >> 16 << SM_MAN_BITS) | (unsigned)m;
+        unsigned bv = l >= g && l < k ? best[w] : 0u;
+        uint64_t ok = ballot(key < bv);
+        for (int b = max(g, k); !ok && b < n; b += LLP_WAVE) {   // past the table: the list and the rank
+            const int p = b + l < n ? sm_pair(a, m, b + l) : 0;
+            w = p & 0xffff;
+            key = ((unsigned)p >> 16 << SM_MAN_BITS) | (unsigned)m;
+            bv = b + l < n ? best[w] : 0u;
+            ok = ballot(key < bv);
+            at = b;
+        }
+        if (!ok) {
+            if (l == 0) *bad = 1;   // he exhausted his list
+            return false;
+        }
+        const int i = __ffsll((long long)ok) - 1;
+        at = max(at, 0) + i;
+        if constexpr (LIMIT) tries += at + 1 - g;
+        const int wi = __builtin_amdgcn_readlane(w, i);
+        const unsigned ki = (unsigned)__builtin_amdgcn_readlane((int)key, i);
+        const unsigned seen = (unsigned)__builtin_amdgcn_readlane((int)bv, i);
+        // her holder's row and position, on the way while he is displaced
+        const int m2 = seen == SM_FREE ? m : (int)(seen & SM_MAN);
+        const int row2 = l < k ? a.combo[m2 * SM_COMBO + l] : 0;
+        const int g2 = nx[m2];
+        unsigned old = 0;
+        if (l == 0) {
+            nx[m] = (unsigned short)(at + 1);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            old = atomicMin(&best[wi], ki);
+        }
+        old = (unsigned)__builtin_amdgcn_readfirstlane((int)old);
+        if (old == SM_FREE) return false;
+        if (old == seen) {
+            m = m2;
+            row = row2;
+            g = __builtin_amdgcn_readfirstlane(g2);
+            if constexpr (LIMIT) ++hop, ++moves;
+        } else if (old < ki) {   // another chain was first: m tries on
+            g = at + 1;
+        } else {                 // another chain's man is displaced instead
+            m = (int)(old & SM_MAN);
+            row = l < k ? a.combo[m * SM_COMBO + l] : 0;
+            g = __builtin_amdgcn_readfirstlane((int)nx[m]);
+            if constexpr (LIMIT) ++hop, ++moves;
+        }
+    }
+    return true;
+}
+
 // A chain step takes the man displaced last, finds the first woman on the
 // rest of his list whose key his own beats, and displaces her holder.  It is
 // bound by latency: a row of the table from the L2, the women's keys from
 // LDS, and the next man is known.  Two forms:
-//  - a thread per chain, 6 women per step, while there is a chain for every
-//    thread: up to SM_HOPS steps per man, then the man of the moment is parked;
-//  - a wave per chain for the parked men (the chains that are left are few
-//    and long): a lane per list position, so a man's whole row of 64 is one
-//    load and a ballot finds his woman, however many reject him.  Her holder
-//    is in the key read, so his row is loaded before the atomicMin that
+//  - a thread per chain, 6 women per step;
+//  - a wave per chain: a lane per list position, so a man's whole row of 64 is
+//    one load and a ballot finds his woman, however many reject him.  Her
+//    holder is in the key read, so his row is loaded before the atomicMin that
 //    displaces him returns; if another chain came between, the row is dropped.
+// The first pass starts every man by a thread, SM_HOPS steps inside the table,
+// and a pass leaves its unfinished chains to the next.  In a random market few
+// are left, and waves end them.  Where many are, waves displace at most
+// SM_WAVE_HOPS men per chain and pass, so that good ranks settle before the
+// rest try on, and while a displaced man tries few positions (SM_TRIES), many
+// chains at once by threads are the faster.  That is what lists and ranks much
+// alike need: all lists and ranks the same, n = 3000 18.7 ms (ranks reversed
+// 18.3, shuffled 23.0), n = 8192 117 (119, 184), against 47.6 (182, 194) and 444
+// (1590, 1630) with every chain run to its end by a wave, and 15.8 (21.9, 29.6)
+// and 91 (151, 243) with a thread per chain throughout.  Lists alike with random
+// ranks want waves: n = 8192 39.8 ms against 53.4 by threads.  Limits of 24 to
+// 200 positions and 64 to 256 chains measure within 10% of each other but for
+// lists and ranks strongly alike at n = 1000 (0.56 ms; 1.10 with 24) and lists
+// alike at n = 300 (0.09; 0.18 with 64 chains).
 // A man's position nx (the next one to try) is written before the atomicMin
 // that places him (LDS operations of a wave stay in order), so whoever reads
 // his key reads his position too.
-// Whole solves, three random markets each: n = 8192 522-1202 us (4.55-5.49 ms
-// with a thread per chain throughout), n = 3000 203-294, n = 1000 155-207 us.
-// Without the first form 962-1626 us at n = 8192, with 4 or 64 steps in it
-// 589-1261 and 517-1192; without touching the table first 572-1341.
+// Random markets, three each: n = 8192 330-521 us (0.73-1.62 ms with a thread per
+// chain throughout), n = 3000 143-239 (335-663), n = 1000 91-109 (192-270).  With 4
+// or 64 steps in the first pass 10% more or the same at n = 8192; without
+// touching the table first 10% more.
 __global__ void __launch_bounds__(SM_LDS_THREADS) k_sm_lds(SArgs a) {
     __shared__ unsigned best[SM_LDS_MAX];
     __shared__ unsigned short nx[SM_LDS_MAX];
-    __shared__ unsigned short pend[SM_LDS_MAX];
-    __shared__ int npend, head, bad;
+    __shared__ unsigned short pend[2][SM_LDS_MAX];
+    // by pass modulo 3: unfinished chains, positions tried and men displaced in
+    // the pass before, chains taken by the waves
+    __shared__ int npend[3], ntry[3], nmove[3], head[3], bad;
     SCtrl* c = a.ctrl;
     const int n = a.n, k = min(n, SM_COMBO), l = lane();
     for (int i = threadIdx.x; i < n; i += SM_LDS_THREADS) {
         best[i] = SM_FREE;
         nx[i] = 0;
     }
-    if (threadIdx.x == 0) npend = head = bad = 0;
+    if (threadIdx.x < 3) npend[threadIdx.x] = ntry[threadIdx.x] = nmove[threadIdx.x] = head[threadIdx.x] = 0;
+    if (threadIdx.x == 0) bad = 0;
     // one word of every line of the table, so that a chain's first visit to a
     // row finds it in this XCD's L2 (the table was written from all of them)
     int x = 0;
     for (int i = threadIdx.x * 32; i < n * SM_COMBO; i += SM_LDS_THREADS * 32) x |= a.combo[i];
     asm volatile("" ::"v"(x));
     __syncthreads();
-    for (int t = threadIdx.x; t < n; t += SM_LDS_THREADS) {
-        int m = t, g = 0;
-        bool park = true;
-        for (int hop = 0; hop < SM_HOPS && g < k; ++hop) {
-            // positions past the table's end read its last entry, whose woman
-            // is then taken only at her own position
-            int cw[SM_LDS_LOOKAHEAD];
-            unsigned bv[SM_LDS_LOOKAHEAD];
-#pragma unroll
-            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) cw[i] = a.combo[m * SM_COMBO + min(g + i, k - 1)];
-#pragma unroll
-            for (int i = 0; i < SM_LDS_LOOKAHEAD; ++i) bv[i] = best[cw[i] & 0xffff];
-            int at = -1, w = 0;
-            unsigned key = 0;
-#pragma unroll
-            for (int i = SM_LDS_LOOKAHEAD - 1; i >= 0; --i) {
-                const unsigned ki = ((unsigned)cw[i] >> 16 << SM_MAN_BITS) | (unsigned)m;
-                if (g + i < k && ki < bv[i]) {
-                    at = g + i;
-                    w = cw[i] & 0xffff;
-                    key = ki;
+    {
+        int tries = 0, moves = 0;
+        for (int t = threadIdx.x; t < n; t += SM_LDS_THREADS) {
+            int m = t, g = 0;
+            if (sm_thread_chain<false>(a, best, nx, SM_HOPS, m, g, tries, moves)) {
+                nx[m] = (unsigned short)g;
+                pend[0][atomicAdd(&npend[0], 1)] = (unsigned short)m;
+            }
+        }
+        sm_add(&ntry[0], tries, &nmove[0], moves);
+    }
+    __syncthreads();
+    for (int pass = 0;; ++pass) {
+        const int i = pass % 3, nxt = (pass + 1) % 3, clr = (pass + 2) % 3;
+        const int np = npend[i];
+        if (np == 0) break;
+        const bool by_thread = np >= SM_MANY && (long long)SM_TRIES * nmove[i] > ntry[i];
+        const unsigned short* from = pend[pass & 1];
+        unsigned short* to = pend[(pass + 1) & 1];
+        if (threadIdx.x == 0) npend[clr] = ntry[clr] = nmove[clr] = head[clr] = 0;   // last read in the pass before
+        int tries = 0, moves = 0;
+        if (by_thread) {
+            for (int t = threadIdx.x; t < np; t += SM_LDS_THREADS) {
+                int m = from[t], g = nx[m];
+                if (!sm_thread_chain<true>(a, best, nx, SM_PASS_HOPS, m, g, tries, moves)) continue;
+                if (g >= n) {
+                    bad = 1;   // he exhausted his list
+                    continue;
+                }
+                nx[m] = (unsigned short)g;
+                to[atomicAdd(&npend[nxt], 1)] = (unsigned short)m;
+            }
+        } else {
+            for (;;) {
+                int q = 0;
+                if (l == 0) q = atomicAdd(&head[i], 1);
+                q = __builtin_amdgcn_readfirstlane(q);
+                if (q >= np) break;
+                int m = __builtin_amdgcn_readfirstlane((int)from[q]);
+                int g = __builtin_amdgcn_readfirstlane((int)nx[m]);
+                if (np <= SM_FEW) {
+                    sm_wave_chain<false>(a, best, nx, &bad, 0, m, g, tries, moves);
+                } else if (sm_wave_chain<true>(a, best, nx, &bad, SM_WAVE_HOPS, m, g, tries, moves) && l == 0) {
+                    nx[m] = (unsigned short)g;
+                    to[atomicAdd(&npend[nxt], 1)] = (unsigned short)m;
                 }
             }
-            if (at < 0) {
-                g = min(g + SM_LDS_LOOKAHEAD, k);
-                continue;
-            }
-            nx[m] = (unsigned short)(at + 1);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            const unsigned old = atomicMin(&best[w], key);
-            if (old == SM_FREE) {
-                park = false;
-                break;
-            }
-            if (old > key) {
-                m = (int)(old & SM_MAN);
-                g = nx[m];
-            } else {
-                g = at + 1;
-            }
+            if (l) tries = moves = 0;   // counted once for the wave
         }
-        if (park) {
-            nx[m] = (unsigned short)g;
-            pend[atomicAdd(&npend, 1)] = (unsigned short)m;
-        }
+        sm_add(&ntry[nxt], tries, &nmove[nxt], moves);
+        __syncthreads();
     }
-    __syncthreads();
-    const int np = npend;
-    for (;;) {
-        int q = 0;
-        if (l == 0) q = atomicAdd(&head, 1);
-        q = __builtin_amdgcn_readfirstlane(q);
-        if (q >= np) break;
-        int m = __builtin_amdgcn_readfirstlane((int)pend[q]);
-        int row = l < k ? a.combo[m * SM_COMBO + l] : 0;
-        int g = __builtin_amdgcn_readfirstlane((int)nx[m]);
-        for (;;) {
-            // the first of m's women from position g on who prefers him
-            int at = -1, w = row & 0xffff;
-            unsigned key = ((unsigned)row >> 16 << SM_MAN_BITS) | (unsigned)m;
-            unsigned bv = l >= g && l < k ? best[w] : 0u;
-            uint64_t ok = ballot(key < bv);
-            for (int b = max(g, k); !ok && b < n; b += LLP_WAVE) {   // past the table: the list and the rank
-                const int p = b + l < n ? sm_pair(a, m, b + l) : 0;
-                w = p & 0xffff;
-                key = ((unsigned)p >> 16 << SM_MAN_BITS) | (unsigned)m;
-                bv = b + l < n ? best[w] : 0u;
-                ok = ballot(key < bv);
-                at = b;
-            }
-            if (!ok) {
-                if (l == 0) bad = 1;   // he exhausted his list
-                break;
-            }
-            const int i = __ffsll((long long)ok) - 1;
-            at = max(at, 0) + i;
-            const int wi = __builtin_amdgcn_readlane(w, i);
-            const unsigned ki = (unsigned)__builtin_amdgcn_readlane((int)key, i);
-            const unsigned seen = (unsigned)__builtin_amdgcn_readlane((int)bv, i);
-            // her holder's row and position, on the way while he is displaced
-            const int m2 = seen == SM_FREE ? m : (int)(seen & SM_MAN);
-            const int row2 = l < k ? a.combo[m2 * SM_COMBO + l] : 0;
-            const int g2 = nx[m2];
-            unsigned old = 0;
-            if (l == 0) {
-                nx[m] = (unsigned short)(at + 1);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                old = atomicMin(&best[wi], ki);
-            }
-            old = (unsigned)__builtin_amdgcn_readfirstlane((int)old);
-            if (old == SM_FREE) break;
-            if (old == seen) {
-                m = m2;
-                row = row2;
-                g = __builtin_amdgcn_readfirstlane(g2);
-            } else if (old < ki) {   // another chain was first: m tries on
-                g = at + 1;
-            } else {                 // another chain's man is displaced instead
-                m = (int)(old & SM_MAN);
-                row = l < k ? a.combo[m * SM_COMBO + l] : 0;
-                g = __builtin_amdgcn_readfirstlane((int)nx[m]);
-            }
-        }
-    }
-    __syncthreads();
     if (bad && threadIdx.x == 0) set_status(&c->status, LLP_E_INFEASIBLE);
     // a man's proposals are the positions he tried
     long long made = 0;
