@@ -85,8 +85,8 @@ __device__ __forceinline__ void batch_one(const BArgs& a, int i, int* lds, int* 
             const int* ptr = a.pool + d.in_off;
             const int* dst = ptr + n + 1;
             const int* wgt = dst + m;
-            st = sssp_wg<SS_PER, false, true>(ptr, dst, wgt, n, (int)m, src, sssp_wg_carve<SS_PER>(lds, n), sfl,
-                                      a.out_pool + d.out_off, n + 2);
+            st = sssp_wg<SS_PER, false, true, false>(ptr, dst, wgt, n, (int)m, src, sssp_wg_carve<SS_PER, false>(lds, n), sfl, nullptr,
+                                             a.out_pool + d.out_off, n + 2);
         }
     } else {
         st = LLP_E_INPUT;

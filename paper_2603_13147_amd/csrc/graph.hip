@@ -1720,22 +1720,27 @@ __global__ void k_graph_decode(int* G, int n) {
 // --------------------------------------------------------------- small graphs
 // A graph whose state and row offsets fit in one CU's LDS, solved by one
 // workgroup in one launch (sssp_wg.h): its rounds are separated by a workgroup
-// barrier (about 2 us each) instead of a launch over 512 list segments (10 to
-// 19 us each).  One CU pushes about 0.8 G arcs a second, so the number of
-// arcs sets the limit: uniform graphs of 8 arcs per vertex take 47 us instead
-// of 135 (n = 64), 133 instead of 294 (n = 4096), 284 instead of 336 (n =
-// 12000, 108 K arcs) and 439 instead of 398 (n = 16384, 147 K arcs); R-MAT
-// graphs 153 instead of 215 us (70 K arcs) and 238 instead of 198 (139 K).
-constexpr int SMALL_N = 16384;     // 137 KB of LDS
+// barrier (about 2 us each) instead of a launch (10 to 19 us each over 512 list
+// segments).  One CU pushes about 0.8 G arcs a second, so the number of arcs
+// sets the limit, and a lower one for few vertices, whose search the grid-wide
+// rounds end in three or four.  Uniform graphs, SSSP, in us here and by
+// grid-wide rounds: 8 arcs per vertex n = 64 36 / 120, n = 4096 118 / 320, 1000 arcs
+// per vertex n = 64 77 / 89; at the limits n = 64, 48 K arcs 67 / 96, n = 256, 62 K
+// 112 / 120, n = 512, 75 K 133 / 180, n = 960, 93 K 186 / 204, n = 4096, 98 K 204 / 252;
+// past them n = 64, 80 K 133 / 99, n = 256, 80 K 339 / 120, n = 512, 100 K 156 / 147,
+// n = 1250, 120 K 191 / 191.  R-MAT graphs of 70 K arcs, scale 12 144 / 179.
+constexpr int SMALL_N = 16384;     // 142 KB of LDS
 constexpr int SMALL_M = 100000;
+constexpr long long SMALL_M0 = 50000, SMALL_M1 = 50;   // and at most M0 + M1 n
 constexpr int SMALL_T = 1024;
-constexpr int SMALL_PER = 4;       // 8: 143 us at n = 4096, 12: 162
+constexpr int SMALL_PER = 4;       // 8: 143 us at n = 4096 instead of 133, 12: 162
 
 // Below 3 arcs per vertex a graph may be a chain, through which the grid-wide
 // push rounds walk 32 steps each; weighted meshes want the buckets of the
 // grid-wide rounds (a 64^2 grid: 479 us here, 303 there; 16^2: 49 and 87).
 static bool small_graph(int n, long long m, const SchedParams& sp) {
-    return n <= SMALL_N && m <= SMALL_M && m >= 3ll * n && (sp.push_dclass != DCLS_WIDE || n <= 1024);
+    return n <= SMALL_N && m <= SMALL_M && m <= SMALL_M0 + SMALL_M1 * n && m >= 3ll * n &&
+           (sp.push_dclass != DCLS_WIDE || n <= 1024);
 }
 
 template <bool UNIT>
@@ -1743,9 +1748,9 @@ __global__ void __launch_bounds__(SMALL_T) k_graph_small(int n, int m, const int
                                                          const int* out_w, int source, int* dist, long long max_rounds,
                                                          int* status) {
     __shared__ unsigned long long lds[(sssp_wg_words(SMALL_N, SMALL_T, SMALL_PER) + 1) / 2];
-    __shared__ int fl[SW_FLAGS];
-    const int st = sssp_wg<SMALL_PER, UNIT, false>(out_ptr, out_dst, out_w, n, m, source, sssp_wg_carve<SMALL_PER>(lds, n),
-                                                   fl, dist, max_rounds);
+    __shared__ int fl[SW_FLAGS], share[SW_SHARE_WORDS];
+    const int st = sssp_wg<SMALL_PER, UNIT, false, true>(out_ptr, out_dst, out_w, n, m, source,
+                                                         sssp_wg_carve<SMALL_PER, true>(lds, n), fl, share, dist, max_rounds);
     if (threadIdx.x == 0) *status = st;
 }
 

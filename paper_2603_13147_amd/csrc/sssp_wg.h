@@ -23,6 +23,23 @@
 // 1024: 820).
 // A round is one scan of the bitmap; within a round waves see each other's
 // advances, so a round is at least a synchronous one.
+//
+// SOLO: one graph alone on the chip, 16 waves, so a round lasts as long as its
+// busiest wave, and three things spread the arcs:
+//  - runs of four vertices are dealt to the blocks in turn, to at least one
+//    block per wave (64 vertices of 97 arcs 44 us; 105 in one block), every
+//    turn from another block on, as hubs often share their ids' low bits
+//    (R-MAT scale 10, 60 arcs a vertex, ids not permuted: 135 us, 170 without);
+//  - a wave's blocks with few active vertices make one step together (R-MAT
+//    scale 13, 8 arcs a vertex, BFS: 122 us, 147 without; 183 and 278 with ids
+//    not permuted; uniform n = 4096, 8 arcs, SSSP: 118, 139 without);
+//  - the long rows of a block that has more than SW_HUGE arcs in them are left
+//    to all waves in the next round, in a list (one hub with half of 80000 arcs:
+//    68 us, 212 without).  A list of every long row makes them wait too often
+//    (R-MAT scale 10, 70 arcs a vertex: 111 us with a limit of 4096, 150 with 512).
+// Going on with the blocks while few vertices are active, with or without a
+// look at the other waves, saves rounds but pushes values too early: 5 to 40%
+// longer throughout.  In the batch the other workgroups fill a wave's pauses.
 #pragma once
 
 #include "llp_dev.h"
@@ -36,6 +53,9 @@ constexpr int SW_LONG = 256;    // longest row taken through the table
 // read this one's; the words it reads are cleared no sooner than two rounds
 // on, so all waves leave by the same round); an arc overflowed; a distance did.
 constexpr int SW_TAKEN = 0, SW_BAD = 3, SW_OVF_ARC = 6, SW_OVF = 7, SW_FLAGS = 8;
+// SOLO: log2 of a run's vertices; arcs in a block's long rows above which all
+// waves share them; rows listed for that, by round modulo 3, the length first.
+constexpr int SW_RUN = 2, SW_HUGE = 4096, SW_SHARED = 399, SW_SHARE_WORDS = 3 * (SW_SHARED + 1);
 
 // LDS words needed for n vertices and T threads, n + 1 row offsets among them.
 // per: arc positions per lane and step, a multiple of 4.
@@ -44,19 +64,43 @@ __host__ __device__ constexpr size_t sssp_wg_words(size_t n, size_t T, size_t pe
 }
 
 struct SsspWg {
+    int lg;                    // SOLO: log2 of the count of blocks, which is a multiple of the waves'
     unsigned long long* act;   // active vertices, a word per block of 64
     unsigned char* own;        // the wave's position table
     int* G;
     int* ptr;
 };
 
+// Blocks for n vertices.
+template <bool SOLO>
+__device__ __forceinline__ int sssp_wg_blocks(const SsspWg& s, int n) {
+    return SOLO ? 1 << s.lg : (n + 63) >> 6;
+}
+// SOLO: where a turn of dealing runs to the blocks differs from the first.
+__device__ __forceinline__ int sssp_wg_turn(const SsspWg& s, int turn) { return turn * 45 & ((1 << s.lg) - 1); }
+// The vertex of a lane of a block.
+template <bool SOLO>
+__device__ __forceinline__ int sssp_wg_vertex(const SsspWg& s, int blk, int l) {
+    if (!SOLO) return blk * 64 + l;
+    const int turn = l >> SW_RUN;
+    return (turn << s.lg | (blk ^ sssp_wg_turn(s, turn))) << SW_RUN | (l & ((1 << SW_RUN) - 1));
+}
+// The index of a vertex' bit in the bitmap.
+template <bool SOLO>
+__device__ __forceinline__ int sssp_wg_bit(const SsspWg& s, int v) {
+    if (!SOLO) return v;
+    const int run = v >> SW_RUN, turn = run >> s.lg, blk = (run & ((1 << s.lg) - 1)) ^ sssp_wg_turn(s, turn);
+    return blk << 6 | turn << SW_RUN | (v & ((1 << SW_RUN) - 1));
+}
+
 // lds: 8-byte aligned, sssp_wg_words(n, blockDim.x, PER) words.
-template <int PER>
+template <int PER, bool SOLO>
 __device__ __forceinline__ SsspWg sssp_wg_carve(void* lds, int n) {
     SsspWg s;
-    const int nb = (n + 63) >> 6;
+    s.lg = 4;   // SOLO has 16 waves
+    while (SOLO && 64 << s.lg < n) ++s.lg;
     s.act = (unsigned long long*)lds;
-    unsigned char* own = (unsigned char*)(s.act + nb);
+    unsigned char* own = (unsigned char*)(s.act + sssp_wg_blocks<SOLO>(s, n));
     s.own = own + (threadIdx.x >> 6) * LLP_WAVE * PER;
     s.G = (int*)(own + (blockDim.x >> 6) * LLP_WAVE * PER);
     s.ptr = s.G + n;
@@ -64,15 +108,18 @@ __device__ __forceinline__ SsspWg sssp_wg_carve(void* lds, int n) {
 }
 
 // One arc's advance.
+template <bool SOLO>
 __device__ __forceinline__ void sssp_wg_push(const SsspWg& s, int x, int cand) {
-    if (cand > s.G[x] && atomicMax(&s.G[x], cand) < cand)
-        atomicOr(&((unsigned*)s.act)[x >> 5], 1u << (x & 31));
+    if (cand > s.G[x] && atomicMax(&s.G[x], cand) < cand) {
+        const int b = sssp_wg_bit<SOLO>(s, x);
+        atomicOr(&((unsigned*)s.act)[b >> 5], 1u << (b & 31));
+    }
 }
 
 // Arcs ks[j] of tails with state gs[j] (j < PER, those with on[j]).  UNIT: every
 // weight is 1.  NEG: negative weights are malformed input, else they are
 // taken as they are.
-template <int PER, bool UNIT, bool NEG>
+template <int PER, bool UNIT, bool NEG, bool SOLO>
 __device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, const int* wgt, int n, const int* ks,
                                              const int* gs, const bool* on, bool& bad, bool& ovf) {
     int x[PER], w[PER];
@@ -90,23 +137,44 @@ __device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, co
         }
         const int cand = (int)((unsigned)gs[j] - (unsigned)w[j]);
         if (cand <= 0) ovf = true;
-        else sssp_wg_push(s, x[j], cand);
+        else sssp_wg_push<SOLO>(s, x[j], cand);
+    }
+}
+
+// Arcs of one row [zb, zb + zd) of a tail with state zg: positions k0, k0 +
+// step, ... on, CHUNK at a time (uniform in the wave).
+template <int PER, bool UNIT, bool NEG, bool SOLO>
+__device__ __forceinline__ void sssp_wg_row(const SsspWg& s, const int* dst, const int* wgt, int n, int zb, int zd, int zg,
+                                            unsigned k0, unsigned step, bool& bad, bool& ovf) {
+    for (; k0 < (unsigned)zd; k0 += step) {
+        int ks[PER], gs[PER];
+        bool on[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const unsigned k = k0 + 64 * j + lane();
+            on[j] = k < (unsigned)zd;
+            ks[j] = zb + (int)k;
+            gs[j] = zg;
+        }
+        sssp_wg_arcs<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, ks, gs, on, bad, ovf);
     }
 }
 
 // Solves with the calling workgroup.  gptr[n + 1], dst[m],
 // wgt[m]: out-CSR; dist[n]: the output (INF = unreached).  fl: LDS int[SW_FLAGS].
-// Returns the status, uniform in the workgroup.
-template <int PER, bool UNIT, bool NEG>
+// share: LDS int[SW_SHARE_WORDS] (SOLO).  Returns the status, uniform in the
+// workgroup.
+template <int PER, bool UNIT, bool NEG, bool SOLO>
 __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src,
-                                       const SsspWg& s, int* fl, int* dist, long long max_rounds) {
+                                       const SsspWg& s, int* fl, int* share, int* dist, long long max_rounds) {
     const int T = blockDim.x, t = threadIdx.x, l = lane(), wave = t >> 6, nw = T >> 6;
     constexpr int CHUNK = LLP_WAVE * PER;
-    const int nb = (n + 63) >> 6;
+    const int nb = sssp_wg_blocks<SOLO>(s, n), sb = sssp_wg_bit<SOLO>(s, src);
     for (int v = t; v < n; v += T) s.G[v] = v == src ? LLP_INF : 0;
     for (int v = t; v <= n; v += T) s.ptr[v] = gptr[v];
-    for (int i = t; i < nb; i += T) s.act[i] = i == (src >> 6) ? 1ull << (src & 63) : 0ull;
+    for (int i = t; i < nb; i += T) s.act[i] = i == (sb >> 6) ? 1ull << (sb & 63) : 0ull;
     if (t < SW_FLAGS) fl[t] = 0;
+    if (SOLO && t < 3) share[t * (SW_SHARED + 1)] = 0;
     __syncthreads();
     long long r = 0;
     bool more = true;
@@ -114,20 +182,51 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
     for (; more && r < max_rounds; ++r) {
         bool bad = false, ovf = false, did = false;
         if (t == 0) fl[SW_TAKEN + (r + 1) % 3] = fl[SW_BAD + (r + 1) % 3] = 0;   // last read in round r - 2
+        if constexpr (SOLO) {
+            // the last round's long rows, with what their vertices have risen to
+            // meanwhile; this round fills its own list, the next one's is free
+            const int* list = share + (r + 2) % 3 * (SW_SHARED + 1);
+            const int rows = min(list[0], SW_SHARED);
+            if (t == 0) share[(r + 1) % 3 * (SW_SHARED + 1)] = 0;
+            did = rows > 0;
+            for (int i = 0; i < rows; ++i) {
+                const int v = list[1 + i], zb = s.ptr[v], zd = s.ptr[v + 1] - zb, zg = s.G[v];
+                sssp_wg_row<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, zb, zd, zg, wave * CHUNK, nw * CHUNK, bad, ovf);
+            }
+        }
         for (int c = wave; c < nb; c += nw * LLP_WAVE) {   // lane l looks at block c + nw l
-            uint64_t todo = ballot(c + nw * l < nb && s.act[min(c + nw * l, nb - 1)] != 0ull);
-            for (; todo; todo &= todo - 1) {
+            const unsigned long long mine = c + nw * l < nb ? s.act[min(c + nw * l, nb - 1)] : 0ull;
+            uint64_t todo = ballot(mine != 0ull);
+            // SOLO: all blocks with few active vertices make one step, lane l with
+            // vertex l / per of the (l % per)-th block
+            const int per = SOLO ? nb / nw : 1;
+            uint64_t few = SOLO && per > 1 ? ballot(mine != 0ull && __popcll(mine) * per <= LLP_WAVE) : 0ull;
+            if (few && (few & (few - 1)) == 0ull) few = 0ull;
+            todo &= ~few;
+            while (todo || few) {
                 did = true;
-                const int blk = c + nw * (__ffsll((long long)todo) - 1);
-                // take the block's bits, then read the states: what rises later sets its bit again
-                const unsigned long long f = s.act[blk];
-                __builtin_amdgcn_wave_barrier();
-                if (l == 0) atomicAnd(&s.act[blk], ~f);
+                int v = -1;
+                // take the bits, then read the states: what rises later sets its bit again
+                if (SOLO && few) {
+                    const bool in = (few >> l) & 1ull;
+                    if (in) atomicAnd(&s.act[c + nw * l], ~mine);
+                    const int i = l & (per - 1);
+                    unsigned long long f = (unsigned long long)__shfl((long long)(in ? mine : 0ull), i, LLP_WAVE);
+                    for (int k = l / per; k > 0; --k) f &= f - 1;
+                    if (f) v = sssp_wg_vertex<SOLO>(s, c + nw * i, __ffsll((long long)f) - 1);
+                    few = 0ull;
+                } else {
+                    const int blk = c + nw * (__ffsll((long long)todo) - 1);
+                    todo &= todo - 1;
+                    const unsigned long long f = s.act[blk];
+                    __builtin_amdgcn_wave_barrier();
+                    if (l == 0) atomicAnd(&s.act[blk], ~f);
+                    if ((f >> l) & 1ull) v = sssp_wg_vertex<SOLO>(s, blk, l);
+                }
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_wave_barrier();
                 int b = 0, deg = 0, g = 0;
-                if ((f >> l) & 1ull) {
-                    const int v = blk * 64 + l;
+                if (v >= 0) {
                     b = s.ptr[v];
                     const int e = s.ptr[v + 1];
                     if (b < 0 || e > m || e < b) bad = true;
@@ -174,24 +273,26 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
                         ks[j] = p + shfl(off, w);
                         gs[j] = shfl(g, w);
                     }
-                    sssp_wg_arcs<PER, UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                    sssp_wg_arcs<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, ks, gs, on, bad, ovf);
                     __builtin_amdgcn_wave_barrier();
                 }
-                for (uint64_t big = ballot(deg > SW_LONG); big; big &= big - 1) {
-                    const int z = __ffsll((long long)big) - 1;
-                    const int zb = shfl(b, z), zd = shfl(deg, z), zg = shfl(g, z);
-                    for (unsigned k0 = 0; k0 < (unsigned)zd; k0 += CHUNK) {
-                        int ks[PER], gs[PER];
-                        bool on[PER];
-#pragma unroll
-                        for (int j = 0; j < PER; ++j) {
-                            const unsigned k = k0 + 64 * j + l;
-                            on[j] = k < (unsigned)zd;
-                            ks[j] = zb + (int)k;
-                            gs[j] = zg;
+                uint64_t big = ballot(deg > SW_LONG);
+                if constexpr (SOLO) {
+                    if (big && wave_sum64(deg > SW_LONG ? deg : 0) > SW_HUGE) {
+                        if (deg > SW_LONG) {
+                            int* list = share + r % 3 * (SW_SHARED + 1);
+                            const int i = atomicAdd(&list[0], 1);
+                            if (i < SW_SHARED) {
+                                list[1 + i] = v;
+                                deg = 0;
+                            }
                         }
-                        sssp_wg_arcs<PER, UNIT, NEG>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                        big = ballot(deg > SW_LONG);
                     }
+                }
+                for (; big; big &= big - 1) {
+                    const int z = __ffsll((long long)big) - 1;
+                    sssp_wg_row<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, shfl(b, z), shfl(deg, z), shfl(g, z), 0, CHUNK, bad, ovf);
                 }
             }
         }

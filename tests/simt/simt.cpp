@@ -414,3 +414,5 @@ extern "C" void* simt_alloc(size_t bytes) {
     return p;
 }
 extern "C" void simt_free(void* p) { hipFree(p); }
+// kernel launches so far
+extern "C" unsigned long long simt_launches() { return simt::g_launches; }
