@@ -3,7 +3,7 @@
 //
 // Transitive closure.  State: boolean G[u][v]; (u, v) is forbidden while false
 // if (u, v) is an arc or G[u][w] and G[w][v] for some w.  A workgroup sweeps a
-// group of BITS rows u0 .. u0 + BITS - 1 together, held in LDS by column: word
+// group of rows u0 .. u0 + rows - 1 together, held in LDS by column: word
 // R[v] has bit s set iff G[u0 + s][v].  A vertex w whose word grew is active;
 // taking it sets, for every arc (w, x), the bits of R[w] (and w's own, if it is
 // one of the group's rows) in R[x], and makes x active if that set any.  Each
@@ -60,25 +60,34 @@ __device__ __forceinline__ void tc_set(unsigned* R, unsigned* act, int x, unsign
     if (bits & ~old) atomicOr(&act[x >> 5], 1u << (x & 31));
 }
 
-// One workgroup per group of BITS rows.  LDS: the active bitmap (64-bit words,
-// one per block of 64 vertices), then the words R.
-// What bounds it is the latency of a step (row offsets, arc heads, LDS), so a
-// wave takes the vertices of a block at once, a lane each, 8 arcs in flight
+// One workgroup per group of rows (a power of two, BITS at most).  LDS: the
+// active bitmap (64-bit words, one per block of 64 vertices), then the words R.
+// A wave takes the vertices of a block at once, a lane each, 8 arcs in flight
 // per lane, the next block's row offsets loaded meanwhile; rows of more than
-// TC_LONG arcs are walked by the whole wave.  Going on with a block while it
-// has active vertices saves rounds but costs more visits: 427 us at the size
-// below, and 160 if only while 8 or fewer are.  Most arcs set nothing
-// new: a plain read of R[x] spares them the atomic.  A round is one scan of
-// the bitmap (wave w looks at blocks w + 16 l, lane l; a
-// group of fewer than 16 blocks has a wave per block), so it is short
-// however deep the graph, and a wave sees what the others did meanwhile.
-// n = 8192, 65536 arcs: 138 us, against 2276 with a workgroup per row
+// TC_LONG arcs are walked by the whole wave.  What bounds it on wide searches
+// is how the arcs are read: a lane per vertex touches a line per lane and
+// fetches it again for its next arcs, about 5 clocks per arc and CU (64 K arcs:
+// 137 us).  On deep searches it is the round, about 0.75 us of dependent LDS and
+// L2 trips and of the instructions of 16 waves.  So where no active vertex of
+// a block has more than TC_SHORT arcs a wave reads those alone, and a graph of
+// few vertices makes as many groups as there are CUs, of fewer rows each, which
+// leaves fewer vertices active in a round: a chain of 500 vertices takes 366 us
+// (508 without either, 421 with a workgroup per row), of 1000 with ids permuted
+// 800 (1380 and 835), of 8192 6.0 ms (8.3 and 20.3).
+// Going on with a block while it has active vertices saves rounds but costs
+// more visits: 427 us at the size below, 160 if only while 8 or fewer are, and if
+// only in rounds of few vertices a permuted chain 50% more.  Most arcs set
+// nothing new: a plain read of R[x] spares them the atomic.  A round is one scan
+// of the bitmap (wave w looks at blocks w + 16 l, lane l; a group of fewer than
+// 16 blocks has a wave per block), and a wave sees what the others did meanwhile.
+// n = 8192, 65536 arcs: 131 us, against 2276 with a workgroup per row
 // and a bitmap search each.
 constexpr int TC_BLOCK = 1024;
 constexpr int TC_LONG = 64;
+constexpr int TC_SHORT = 2;   // 4: a chain of 500 vertices 414 us, a band of 4 arcs a vertex 161 instead of 177
 
 template <int BITS>
-__global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* __restrict__ ptr,
+__global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, int rows, const int* __restrict__ ptr,
                                                       const int* __restrict__ dst, unsigned* __restrict__ bits,
                                                       TCtrl* ctl) {
     extern __shared__ unsigned long long tl[];
@@ -90,12 +99,12 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
     const int nb = (n + 63) >> 6, T = blockDim.x, nw = T >> 6;   // nb <= 64 nw
     unsigned* act = (unsigned*)tl;
     unsigned* R = (unsigned*)(tl + nb);
-    const int u0 = blockIdx.x * BITS;
+    const int u0 = blockIdx.x * rows;
     for (int i = t; i < 2 * nb; i += T) {
-        // the group's rows are active: bits u0 .. u0 + BITS - 1 below n
+        // the group's rows are active: bits u0 .. u0 + rows - 1 below n
         const int lo = u0 - 32 * i;
         unsigned f = 0u;
-        if (lo >= 0 && lo < 32) f = (BITS == 32 ? ~0u : 0xffffu) << lo;
+        if (lo >= 0 && lo < 32) f = (~0u >> (32 - rows)) << lo;
         if (32 * i + 32 > n) f &= 32 * i >= n ? 0u : (1u << (n & 31)) - 1u;
         act[i] = f;
     }
@@ -135,7 +144,7 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
                     b = e = 0;
                 }
                 g = tc_get<BITS>(R, w);
-                if (w >= u0 && w < u0 + BITS) g |= 1u << (w - u0);
+                if (w >= u0 && w < u0 + rows) g |= 1u << (w - u0);
             }
             todo &= todo - 1;
             if (todo) {
@@ -144,6 +153,24 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
                 pe = ptr[min(blk * 64 + l + 1, n)];
             }
             const bool wide = e - b > TC_LONG;
+            if (!__any(e - b > TC_SHORT)) {
+                int x[TC_SHORT];
+                unsigned have[TC_SHORT];
+#pragma unroll
+                for (int j = 0; j < TC_SHORT; ++j) x[j] = b + j < e ? dst[b + j] : 0;
+#pragma unroll
+                for (int j = 0; j < TC_SHORT; ++j) {
+                    if ((unsigned)x[j] >= (unsigned)n) {
+                        b2 = true;
+                        x[j] = 0;
+                    }
+                    have[j] = tc_get<BITS>(R, x[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < TC_SHORT; ++j)
+                    if (b + j < e && (g & ~have[j])) tc_set<BITS>(R, act, x[j], g);
+                continue;
+            }
             for (unsigned k0 = b; !wide && k0 < (unsigned)e; k0 += 8) {
                 int x[8];
                 unsigned have[8];
@@ -189,12 +216,19 @@ __global__ void __launch_bounds__(TC_BLOCK) k_tc_rows(int n, int m, const int* _
         const int v = blk * 64 + l;
         const unsigned g = v < n ? tc_get<BITS>(R, v) : 0u;
         uint64_t out = 0;
+        if (rows == BITS) {
 #pragma unroll
-        for (int s = 0; s < BITS; ++s) {
-            const uint64_t col = ballot((g >> s) & 1u);
-            out = l == s ? col : out;
+            for (int s = 0; s < BITS; ++s) {
+                const uint64_t col = ballot((g >> s) & 1u);
+                out = l == s ? col : out;
+            }
+        } else {
+            for (int s = 0; s < rows; ++s) {
+                const uint64_t col = ballot((g >> s) & 1u);
+                out = l == s ? col : out;
+            }
         }
-        if (l < BITS && u0 + l < n) {
+        if (l < rows && u0 + l < n) {
             unsigned* row = bits + (long long)(u0 + l) * words + 2 * blk;
             row[0] = (unsigned)out;
             if (2 * blk + 1 < words) row[1] = (unsigned)(out >> 32);
@@ -224,7 +258,9 @@ int solve_tc(int32_t n, int64_t m, const int32_t* out_ptr, const int32_t* out_ds
     TCtrl* ctl = (TCtrl*)ws;
     // 32 rows per group while their words fit in LDS (132 KB at n = 32768), else 16
     const bool narrow = n > 32768;
-    const int rows = narrow ? 16 : 32;
+    // or fewer, one group per CU
+    int rows = narrow ? 16 : 32;
+    while (rows > 1 && n <= (int64_t)device_info().cus * (rows / 2)) rows /= 2;
     const size_t lds = (size_t)((n + 63) / 64) * 8 + (narrow ? (size_t)(n + 1) / 2 : (size_t)n) * 4;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timing = (o.flags & LLP_TIMING) && o.stats;
@@ -237,7 +273,7 @@ int solve_tc(int32_t n, int64_t m, const int32_t* out_ptr, const int32_t* out_ds
     auto* kernel = narrow ? k_tc_rows<16> : k_tc_rows<32>;
     if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kernel, dim3((n + rows - 1) / rows),
-                       dim3(std::min(TC_BLOCK, (n + 63) / 64 * 64)), lds, st, n, (int)m, out_ptr, out_dst, bits,
+                       dim3(std::min(TC_BLOCK, (n + 63) / 64 * 64)), lds, st, n, (int)m, rows, out_ptr, out_dst, bits,
                        ctl);
     LLP_HIP(hipGetLastError());
     if (timing) LLP_HIP(hipEventRecord(ev1, st));

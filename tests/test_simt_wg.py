@@ -9,12 +9,13 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, os.path.join(HERE, "simt"))
 import build as simt_build  # noqa: E402
+import pytest  # noqa: E402
 import wg_build  # noqa: E402
 
 
-def run(which):
+def run(which, cus=1):
     wg_build.build()
-    env = dict(os.environ, SIMT_CUS="1", SIMT_LAG="1")
+    env = dict(os.environ, SIMT_CUS=str(cus), SIMT_LAG="1")
     asan = simt_build.asan_runtime()
     if asan:
         env["LD_PRELOAD"] = asan
@@ -33,8 +34,10 @@ def test_batch_instances_after_a_malformed_one():
         assert x["bad"] == [2, 2, 2] and x["good"] == [0, 0, 0] and x["equal"], x
 
 
-def test_closures_well_formed_and_not():
-    rows = run("closure")
+@pytest.mark.parametrize("cus", [1, 64])
+def test_closures_well_formed_and_not(cus):
+    """In groups of 32 rows, and (as many groups as CUs) of 16."""
+    rows = run("closure", cus)
     assert len(rows) == 3 * 7
     for x in rows:
         assert x["code"] == 0 and x["equal"] if x["case"].endswith("None") else x["code"] == 2, x
