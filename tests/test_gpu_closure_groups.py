@@ -21,7 +21,7 @@ def closure(n, src, dst):
 
 
 @pytest.mark.parametrize("n,deg", [(k * CUS + d, deg) for k in (1, 2, 4) for d in (-1, 0, 1) for deg in (1, 2, 3)
-                                   if k < 4 or deg < 3] + [(8 * CUS, 1), (8 * CUS + 1, 1)])
+                                   if k < 4 or deg == 3])
 def test_random(n, deg):
     """Every vertex has deg arcs, the last deg + 9."""
     rng = np.random.default_rng(n + deg)
@@ -30,7 +30,7 @@ def test_random(n, deg):
     assert np.array_equal(closure(n, src, dst), oracle.transitive_closure(n, src, dst))
 
 
-@pytest.mark.parametrize("n", [300, 1000, 16 * CUS, 16 * CUS + 1])
+@pytest.mark.parametrize("n", [300, 1000, 8 * CUS, 8 * CUS + 1, 16 * CUS, 16 * CUS + 1])
 def test_chains_and_trees(n):
     """Paths whose rows are known: i reaches the later ones of its chain; a binary tree's vertex its subtree."""
     p = np.random.default_rng(n).permutation(n)
