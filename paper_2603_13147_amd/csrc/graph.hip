@@ -748,7 +748,7 @@ __device__ void push_wave(const GArgs& a, const Src& src, int wb, int we, int r,
     const bool cont = !lq && !a.jobs && src.sv.total_edges <= CONT_EDGES;
     Cursor cur = src.locate(wb);
     int base = wb;
-    int av = src.avail(cur);
+    int av = src.avail(cur, we);
     int4 e = (l < av) ? src.load(cur, l) : make_int4(0, 0, LLP_INF, 0);
     while (base < we) {
         if (av <= 0) {
@@ -764,11 +764,12 @@ __device__ void push_wave(const GArgs& a, const Src& src, int wb, int we, int r,
             return;
         }
         const int done = __popcll(ballot(valid && e.z + e.w <= limit));
-        const Cursor nxt = src.advance(cur, done);
+        Cursor nxt = cur;
         int nav = 0;
         int4 ne = make_int4(0, 0, LLP_INF, 0);
         if (limit < we) {
-            nav = src.avail(nxt);
+            nxt = src.advance(cur, done);
+            nav = src.avail(nxt, we);
             if (l < nav) ne = src.load(nxt, l);
         }
         // the block's entries: value, carry decision, LDS tables
