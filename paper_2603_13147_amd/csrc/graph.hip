@@ -1772,8 +1772,12 @@ static int graph_wgs_per_cu(int chunk) { return chunk > 0 ? (chunk > 8 ? 8 : chu
 // 577 / 166 / 489, of 2.2 M 281 / 715 / 194 / 617 against 285 / 690 / 193 / 579, of
 // 4.5 M 330 / 977 / 219 / 849 against 318 / 903 / 225 / 768; hybrid SSSP and BFS on
 // meshes of 0.36 M arcs 954 and 3776 against 987 and 4918, of 2.0 M 2709 and
-// 9895 against 2768 and 11786.
-constexpr int64_t GRAPH_NARROW_M = 1 << 21;
+// 9895 against 2768 and 11786.  Pull rounds of delta buckets are wide ones and
+// leave the advantage sooner: fixed pull with delta 40 and weights to 100 on
+// uniform graphs of 0.3 M arcs 1207 / 410 against 1279 / 420, of 0.5 M 545 / 170 and 660
+// / 209 (4096 and 16384 vertices) against 520 / 163 and 674 / 206, of 1.0 M 630 /
+// 180 against 556 / 164, of 2.0 M 1235 / 336 against 1043 / 301.
+constexpr int64_t GRAPH_NARROW_M = 1 << 21, GRAPH_NARROW_M_DELTA = 1 << 19;
 // workgroups per CU the autotuner tries (llp_autotune_graph); a solve that
 // leaves the choice to the library (chunk 0) takes the record of its size
 // class, so workspaces sized for chunk 0 hold every candidate
@@ -1942,13 +1946,14 @@ static int solve_graph_core(const llp_graph* g, int32_t source, int32_t* out, co
     if (s) return s;
     hybrid_params(jobs_dur ? LLP_KIND_JOBS : (bfs ? LLP_KIND_BFS : LLP_KIND_SSSP), g->n, g->m, can_push, &a.sp);
 
+    const bool delta_pull = o.sched == LLP_SCHED_FIXED && o.delta > 0 && !(o.flags & (LLP_DENSE | LLP_PUSH));
     int per_cu = graph_wgs_per_cu(o.chunk);
     int need_cu = per_cu;   // the scratch asked for; that of fewer segments is never larger
     if (o.chunk <= 0 && !jobs_dur) {
         int tb = 0, tc = 0;
         if (tune_lookup(bfs ? LLP_KIND_BFS : LLP_KIND_SSSP, g->m, &tb, &tc))
             per_cu = need_cu = std::min(std::max(tc, 1), GRAPH_TUNE_MAX);
-        else if (g->m < GRAPH_NARROW_M)
+        else if (g->m < (delta_pull ? GRAPH_NARROW_M_DELTA : GRAPH_NARROW_M))
             per_cu = 1;
     }
     size_t need = graph_ws(g->n, g->m, need_cu, nullptr, nullptr, 0);
