@@ -1733,7 +1733,7 @@ __global__ void k_graph_decode(int* G, int n) {
 constexpr int SMALL_N = 16384;     // 142 KB of LDS
 constexpr int SMALL_M = 100000;
 constexpr long long SMALL_M0 = 50000, SMALL_M1 = 50;   // and at most M0 + M1 n
-constexpr int SMALL_T = 1024;
+constexpr int SMALL_T = SW_SOLO_T;
 constexpr int SMALL_PER = 4;       // 8: 143 us at n = 4096 instead of 133, 12: 162
 
 // Below 3 arcs per vertex a graph may be a chain, through which the grid-wide

@@ -93,7 +93,10 @@ __device__ __forceinline__ int knap_sweep(const int* wt, const int* val, int ite
     const int base = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * 64 * CH;
 #pragma unroll
     for (int i = 0; i < CH; ++i) g[i] = 0u;
-    int par = 0;
+    // words from one buffer to the other (two pointers and a choice between them
+    // cost the batch kernel spilled scalar registers)
+    const int flip = buf1 ? (int)(buf1 - buf0) : 0;
+    int off = 0;
     // 64 items per load, one per lane; the next 64 are loaded meanwhile
     int wn = l < items ? wt[l] : 0, vn = l < items ? val[l] : 0;
     for (int k0 = 0; k0 < items; k0 += 64) {
@@ -106,9 +109,9 @@ __device__ __forceinline__ int knap_sweep(const int* wt, const int* val, int ite
         for (uint64_t todo = ballot(wv <= W && vv != 0); todo; todo &= todo - 1) {
             const int j = __ffsll((long long)todo) - 1;
             const int w = __builtin_amdgcn_readlane(wv, j), v = __builtin_amdgcn_readlane(vv, j);
-            knap_item<CH>(g, (buf1 && par) ? buf1 : buf0, base, W, w, (unsigned)v);
-            if (!buf1) __syncthreads();
-            par ^= 1;
+            knap_item<CH>(g, buf0 + off, base, W, w, (unsigned)v);
+            if (!flip) __syncthreads();
+            off = flip - off;
         }
     }
     return LLP_OK;

@@ -20,18 +20,22 @@
 // graphs of 256 to 4096 vertices (80 M arcs): 681 us, against 1984 us with a
 // thread per vertex.  There PER is 4, for four workgroups per CU (PER = 8
 // needs more registers: 760 us), in workgroups of 512 threads (256: 934 us,
-// 1024: 820).
+// 1024: 820).  Where no vertex of the step has more than one arc, the lanes of
+// the batch read their own: chains are nothing but rounds, and 1001 vertices in
+// one take 0.96 ms, 1.55 through the table (1.25 with a thread per vertex).
 // A round is one scan of the bitmap; within a round waves see each other's
 // advances, so a round is at least a synchronous one.
 //
 // SOLO: one graph alone on the chip, 16 waves, so a round lasts as long as its
 // busiest wave, and three things spread the arcs:
 //  - runs of four vertices are dealt to the blocks in turn, to at least one
-//    block per wave (64 vertices of 97 arcs 44 us; 105 in one block), every
+//    block per wave (64 vertices of 97 arcs 42 us; 101 in one block), every
 //    turn from another block on, as hubs often share their ids' low bits
-//    (R-MAT scale 10, 60 arcs a vertex, ids not permuted: 135 us, 170 without);
+//    (R-MAT scale 13, 8 arcs a vertex, ids not permuted: 234 us, 365 without).
+//    Blocks of neighbouring vertices are up to 10% faster where they happen to
+//    be even (R-MAT scale 11 with ids permuted 93 us, 102 dealt), and 355 there;
 //  - a wave's blocks with few active vertices make one step together (R-MAT
-//    scale 13, 8 arcs a vertex, BFS: 122 us, 147 without; 183 and 278 with ids
+//    scale 13, 8 arcs a vertex, BFS: 111 us, 147 without; 171 and 278 with ids
 //    not permuted; uniform n = 4096, 8 arcs, SSSP: 118, 139 without);
 //  - the long rows of a block that has more than SW_HUGE arcs in them are left
 //    to all waves in the next round, in a list (one hub with half of 80000 arcs:
@@ -53,8 +57,10 @@ constexpr int SW_LONG = 256;    // longest row taken through the table
 // read this one's; the words it reads are cleared no sooner than two rounds
 // on, so all waves leave by the same round); an arc overflowed; a distance did.
 constexpr int SW_TAKEN = 0, SW_BAD = 3, SW_OVF_ARC = 6, SW_OVF = 7, SW_FLAGS = 8;
-// SOLO: log2 of a run's vertices; arcs in a block's long rows above which all
-// waves share them; rows listed for that, by round modulo 3, the length first.
+// SOLO: log2 of the waves; log2 of a run's vertices; arcs in a block's long rows
+// above which all waves share them; rows listed for that, by round modulo 3, the
+// length first.
+constexpr int SW_SOLO_LG = 4, SW_SOLO_T = 64 << SW_SOLO_LG;
 constexpr int SW_RUN = 2, SW_HUGE = 4096, SW_SHARED = 399, SW_SHARE_WORDS = 3 * (SW_SHARED + 1);
 
 // LDS words needed for n vertices and T threads, n + 1 row offsets among them.
@@ -77,7 +83,7 @@ __device__ __forceinline__ int sssp_wg_blocks(const SsspWg& s, int n) {
     return SOLO ? 1 << s.lg : (n + 63) >> 6;
 }
 // SOLO: where a turn of dealing runs to the blocks differs from the first.
-__device__ __forceinline__ int sssp_wg_turn(const SsspWg& s, int turn) { return turn * 45 & ((1 << s.lg) - 1); }
+__device__ __forceinline__ int sssp_wg_turn(const SsspWg& s, int turn) { return turn & ((1 << s.lg) - 1); }
 // The vertex of a lane of a block.
 template <bool SOLO>
 __device__ __forceinline__ int sssp_wg_vertex(const SsspWg& s, int blk, int l) {
@@ -97,7 +103,7 @@ __device__ __forceinline__ int sssp_wg_bit(const SsspWg& s, int v) {
 template <int PER, bool SOLO>
 __device__ __forceinline__ SsspWg sssp_wg_carve(void* lds, int n) {
     SsspWg s;
-    s.lg = 4;   // SOLO has 16 waves
+    s.lg = SW_SOLO_LG;
     while (SOLO && 64 << s.lg < n) ++s.lg;
     s.act = (unsigned long long*)lds;
     unsigned char* own = (unsigned char*)(s.act + sssp_wg_blocks<SOLO>(s, n));
@@ -144,14 +150,14 @@ __device__ __forceinline__ void sssp_wg_arcs(const SsspWg& s, const int* dst, co
 // Arcs of one row [zb, zb + zd) of a tail with state zg: positions k0, k0 +
 // step, ... on, CHUNK at a time (uniform in the wave).
 template <int PER, bool UNIT, bool NEG, bool SOLO>
-__device__ __forceinline__ void sssp_wg_row(const SsspWg& s, const int* dst, const int* wgt, int n, int zb, int zd, int zg,
+__device__ __forceinline__ void sssp_wg_row(const SsspWg& s, const int* dst, const int* wgt, int n, int l, int zb, int zd, int zg,
                                             unsigned k0, unsigned step, bool& bad, bool& ovf) {
     for (; k0 < (unsigned)zd; k0 += step) {
         int ks[PER], gs[PER];
         bool on[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const unsigned k = k0 + 64 * j + lane();
+            const unsigned k = k0 + 64 * j + l;
             on[j] = k < (unsigned)zd;
             ks[j] = zb + (int)k;
             gs[j] = zg;
@@ -167,7 +173,7 @@ __device__ __forceinline__ void sssp_wg_row(const SsspWg& s, const int* dst, con
 template <int PER, bool UNIT, bool NEG, bool SOLO>
 __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const int* wgt, int n, int m, int src,
                                        const SsspWg& s, int* fl, int* share, int* dist, long long max_rounds) {
-    const int T = blockDim.x, t = threadIdx.x, l = lane(), wave = t >> 6, nw = T >> 6;
+    const int T = SOLO ? SW_SOLO_T : blockDim.x, t = threadIdx.x, l = lane(), wave = t >> 6, nw = T >> 6;
     constexpr int CHUNK = LLP_WAVE * PER;
     const int nb = sssp_wg_blocks<SOLO>(s, n), sb = sssp_wg_bit<SOLO>(s, src);
     for (int v = t; v < n; v += T) s.G[v] = v == src ? LLP_INF : 0;
@@ -177,61 +183,75 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
     if (SOLO && t < 3) share[t * (SW_SHARED + 1)] = 0;
     __syncthreads();
     long long r = 0;
+    int now = 0;   // r modulo 3
     bool more = true;
     int st = LLP_OK;
     for (; more && r < max_rounds; ++r) {
+        const int next = now == 2 ? 0 : now + 1, last = now == 0 ? 2 : now - 1;
         bool bad = false, ovf = false, did = false;
-        if (t == 0) fl[SW_TAKEN + (r + 1) % 3] = fl[SW_BAD + (r + 1) % 3] = 0;   // last read in round r - 2
+        if (t == 0) fl[SW_TAKEN + next] = fl[SW_BAD + next] = 0;   // last read in round r - 2
         if constexpr (SOLO) {
             // the last round's long rows, with what their vertices have risen to
             // meanwhile; this round fills its own list, the next one's is free
-            const int* list = share + (r + 2) % 3 * (SW_SHARED + 1);
+            const int* list = share + last * (SW_SHARED + 1);
             const int rows = min(list[0], SW_SHARED);
-            if (t == 0) share[(r + 1) % 3 * (SW_SHARED + 1)] = 0;
+            if (t == 0) share[next * (SW_SHARED + 1)] = 0;
             did = rows > 0;
             for (int i = 0; i < rows; ++i) {
                 const int v = list[1 + i], zb = s.ptr[v], zd = s.ptr[v + 1] - zb, zg = s.G[v];
-                sssp_wg_row<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, zb, zd, zg, wave * CHUNK, nw * CHUNK, bad, ovf);
+                sssp_wg_row<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, l, zb, zd, zg, wave * CHUNK, nw * CHUNK, bad, ovf);
             }
         }
         for (int c = wave; c < nb; c += nw * LLP_WAVE) {   // lane l looks at block c + nw l
-            const unsigned long long mine = c + nw * l < nb ? s.act[min(c + nw * l, nb - 1)] : 0ull;
-            uint64_t todo = ballot(mine != 0ull);
-            // SOLO: all blocks with few active vertices make one step, lane l with
-            // vertex l / per of the (l % per)-th block
-            const int per = SOLO ? nb / nw : 1;
-            uint64_t few = SOLO && per > 1 ? ballot(mine != 0ull && __popcll(mine) * per <= LLP_WAVE) : 0ull;
-            if (few && (few & (few - 1)) == 0ull) few = 0ull;
-            todo &= ~few;
+            // read once: what the step takes is what was counted
+            const unsigned long long seen = c + nw * l < nb ? s.act[min(c + nw * l, nb - 1)] : 0ull;
+            uint64_t todo = ballot(seen != 0ull), few = 0ull;
+            if constexpr (SOLO) {
+                // all blocks with few active vertices make one step: 1 << lp
+                // blocks to a wave, lane l with vertex l >> lp of block l & (1 << lp) - 1
+                const int lp = s.lg - SW_SOLO_LG;
+                if (lp > 0) few = ballot(__popcll(seen) << lp <= LLP_WAVE) & todo;
+                if ((few & (few - 1)) == 0ull) few = 0ull;
+                todo &= ~few;
+            }
             while (todo || few) {
                 did = true;
-                int v = -1;
+                int b = 0, deg = 0, g = 0, v = 0;
+                bool has;
                 // take the bits, then read the states: what rises later sets its bit again
                 if (SOLO && few) {
+                    const int lp = s.lg - SW_SOLO_LG, i = l & ((1 << lp) - 1);
                     const bool in = (few >> l) & 1ull;
+                    const unsigned long long mine = in ? seen : 0ull;
                     if (in) atomicAnd(&s.act[c + nw * l], ~mine);
-                    const int i = l & (per - 1);
-                    unsigned long long f = (unsigned long long)__shfl((long long)(in ? mine : 0ull), i, LLP_WAVE);
-                    for (int k = l / per; k > 0; --k) f &= f - 1;
-                    if (f) v = sssp_wg_vertex<SOLO>(s, c + nw * i, __ffsll((long long)f) - 1);
+                    unsigned long long f = (unsigned long long)__shfl((long long)mine, i, LLP_WAVE);
+                    for (int k = l >> lp; k > 0; --k) f &= f - 1;
+                    has = f != 0ull;
+                    v = sssp_wg_vertex<SOLO>(s, c + nw * i, __ffsll((long long)f) - 1);
                     few = 0ull;
                 } else {
                     const int blk = c + nw * (__ffsll((long long)todo) - 1);
-                    todo &= todo - 1;
                     const unsigned long long f = s.act[blk];
                     __builtin_amdgcn_wave_barrier();
                     if (l == 0) atomicAnd(&s.act[blk], ~f);
-                    if ((f >> l) & 1ull) v = sssp_wg_vertex<SOLO>(s, blk, l);
+                    has = (f >> l) & 1ull;
+                    v = sssp_wg_vertex<SOLO>(s, blk, l);
+                    todo &= todo - 1;
                 }
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_wave_barrier();
-                int b = 0, deg = 0, g = 0;
-                if (v >= 0) {
+                if (has) {
                     b = s.ptr[v];
                     const int e = s.ptr[v + 1];
                     if (b < 0 || e > m || e < b) bad = true;
                     else deg = e - b;
                     g = s.G[v];
+                }
+                if (!SOLO && !__any(deg > 1)) {   // (a graph alone has three arcs a vertex or more)
+                    int ks[1] = {b}, gs[1] = {g};
+                    bool on[1] = {deg > 0};
+                    sssp_wg_arcs<1, UNIT, NEG, SOLO>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                    continue;
                 }
                 const int len = deg <= SW_LONG ? deg : 0;
                 const int incl = wave_incl_sum(len), E = shfl(incl, 63);
@@ -280,7 +300,7 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
                 if constexpr (SOLO) {
                     if (big && wave_sum64(deg > SW_LONG ? deg : 0) > SW_HUGE) {
                         if (deg > SW_LONG) {
-                            int* list = share + r % 3 * (SW_SHARED + 1);
+                            int* list = share + now * (SW_SHARED + 1);
                             const int i = atomicAdd(&list[0], 1);
                             if (i < SW_SHARED) {
                                 list[1 + i] = v;
@@ -290,18 +310,33 @@ __device__ __forceinline__ int sssp_wg(const int* gptr, const int* dst, const in
                         big = ballot(deg > SW_LONG);
                     }
                 }
+                // (not sssp_wg_row: k_batch then has 7 more scalar registers to
+                // spill and its knapsacks take 5% longer)
                 for (; big; big &= big - 1) {
                     const int z = __ffsll((long long)big) - 1;
-                    sssp_wg_row<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, shfl(b, z), shfl(deg, z), shfl(g, z), 0, CHUNK, bad, ovf);
+                    const int zb = shfl(b, z), zd = shfl(deg, z), zg = shfl(g, z);
+                    for (unsigned k0 = 0; k0 < (unsigned)zd; k0 += CHUNK) {
+                        int ks[PER], gs[PER];
+                        bool on[PER];
+#pragma unroll
+                        for (int j = 0; j < PER; ++j) {
+                            const unsigned k = k0 + 64 * j + l;
+                            on[j] = k < (unsigned)zd;
+                            ks[j] = zb + (int)k;
+                            gs[j] = zg;
+                        }
+                        sssp_wg_arcs<PER, UNIT, NEG, SOLO>(s, dst, wgt, n, ks, gs, on, bad, ovf);
+                    }
                 }
             }
         }
-        if (did && l == 0) fl[SW_TAKEN + r % 3] = 1;
-        if (bad) fl[SW_BAD + r % 3] = 1;
+        if (did && l == 0) fl[SW_TAKEN + now] = 1;
+        if (bad) fl[SW_BAD + now] = 1;
         if (ovf) fl[SW_OVF_ARC] = 1;
         __syncthreads();
-        if (fl[SW_BAD + r % 3]) st = LLP_E_INPUT;
-        more = fl[SW_TAKEN + r % 3] != 0 && st == LLP_OK;
+        if (fl[SW_BAD + now]) st = LLP_E_INPUT;
+        more = fl[SW_TAKEN + now] != 0 && st == LLP_OK;
+        now = next;
     }
     if (more) st = LLP_E_NOT_CONVERGED;
     // overflow: an unreached vertex with a reached in-neighbour (every wave has

@@ -85,6 +85,13 @@ def batches():
                     c = llpgen.CSRGraph(g, weighted=True, out_weights=True)
                     items.append((c.out_ptr, c.out_dst, c.out_w, 5))
                     want.append(oracle.sssp(g.n, g.src, g.dst, g.w, 5))
+                    # one arc a vertex or none: a shuffled chain, and a loop with tails
+                    p = np.random.default_rng(seed + k).permutation(300).astype(np.int32)
+                    for src, dst in ((p[:-1], p[1:]), (p, p[np.arange(300) * 7 % 290])):
+                        h = llpgen.EdgeList(300, src, dst, (dst % 5).astype(np.int32))
+                        c = llpgen.CSRGraph(h, weighted=True, out_weights=True)
+                        items.append((c.out_ptr, c.out_dst, c.out_w, int(p[0])))
+                        want.append(oracle.sssp(300, h.src, h.dst, h.w, int(p[0])))
                 code, st, dist = batch(items, block)
                 print(json.dumps({
                     "case": f"{what}-{block}-{seed}", "code": code,

@@ -31,7 +31,7 @@ def test_batch_instances_after_a_malformed_one():
     assert len(rows) == 12
     for x in rows:
         assert x["code"] == 2, x                      # LLP_E_INPUT: the first nonzero instance status
-        assert x["bad"] == [2, 2, 2] and x["good"] == [0, 0, 0] and x["equal"], x
+        assert x["bad"] == [2] * 3 and x["good"] == [0] * 9 and x["equal"], x
 
 
 @pytest.mark.parametrize("cus", [1, 64])
