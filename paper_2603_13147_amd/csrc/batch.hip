@@ -98,11 +98,14 @@ __device__ __forceinline__ void batch_one(const BArgs& a, int i, int* lds, int* 
     __syncthreads();   // LDS is reused by the next instance
 }
 
-// Registers for 8 waves per SIMD (four workgroups of 512 on a CU) although a
-// few values then spill: 4096 knapsacks and 4096 graphs take 1001 us, against
-// 1126 us without the bound (66 registers, three workgroups on a CU).
+// Up to 10 cells per thread: registers for 8 waves per SIMD (four workgroups of
+// 512 on a CU) although a few values then spill: 4096 knapsacks of W to 4096 and
+// 4096 graphs take 984 us, against 1126 without the bound (66 registers, three
+// workgroups on a CU).  Wider rows leave LDS for two or three workgroups, and
+// the 32 registers of 16 cells and their shifted ones spill: 1000 knapsacks of 100
+// items at W = 5500 and 8191 take 172 and 215 us, against 190 and 263 with it.
 template <int CH>
-__global__ void __launch_bounds__(ch_max_block(CH), CH <= 16 ? 8 : 1) k_batch(BArgs a) {
+__global__ void __launch_bounds__(ch_max_block(CH), CH <= 10 ? 8 : CH <= 16 ? 4 : 1) k_batch(BArgs a) {
     extern __shared__ __align__(8) int lds[];
     __shared__ int claim;
     __shared__ int sfl[SW_FLAGS];

@@ -161,7 +161,9 @@ __device__ __forceinline__ int knap_wg(const int* wt, const int* val, int items,
 }
 
 // --------------------------------------------------------------- host
-// Kernels are compiled for these largest counts of cells per thread.
+// Kernels are compiled for these largest counts of cells per thread: powers of
+// two, and 10 for rows of 4096 to 5119 cells by 512 threads, the widest that the
+// batch kernel takes with registers for 8 waves per SIMD (see k_batch).
 static const int CH_OPTS[] = {4, 8, 10, 16, 32};
 
 static int pick_ch(int W, int T) {
