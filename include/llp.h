@@ -60,9 +60,11 @@ typedef enum {
                                  out-arcs exceed a fraction of all arcs (SSSP 1/3, BFS 1/14, jobs 1/2),
                                  push otherwise (pull without out_w); on weighted graphs of 2 to 8
                                  arcs per vertex the push rounds use the wide delta buckets; a small
-                                 graph (at most 16384 vertices and 100000 arcs, 3 or more per vertex) is
-                                 solved by push rounds in one workgroup when nothing but a workspace,
-                                 a stream and the schedule is asked for */
+                                 graph (at most 16384 vertices, at least 3 arcs per vertex, at most
+                                 100000 arcs and at most 50000 + 50 per vertex; for SSSP above 1024
+                                 vertices at least 8 arcs per vertex) is solved by push rounds in one
+                                 workgroup when nothing but a workspace, a stream and the schedule is
+                                 asked for */
 #define LLP_SCHED_RANDOM  4u  /* per round, a seeded random mode and delta class (schedule-independence tests) */
 #define LLP_SCHED_SCRIPT  5u  /* per round, the code opts->plan[r-1] (plain after the plan ends); used to
                                  measure what a decision at a given round costs when training the scheduler */
@@ -143,8 +145,9 @@ typedef struct {
     volatile int32_t* abort_host; /* [host, pinned] optional: a nonzero value aborts at the next round */
     llp_stats* stats;           /* [host] optional */
     int32_t chunk;              /* launch knob, 0 = default: graph sweeps: workgroups (list segments) per CU
-                                   (default 2, SSSP and BFS of fewer than 2^21 arcs 1; at most 8; pass
-                                   the same opts to llp_workspace_bytes);
+                                   (default 2; 1 for SSSP and BFS of fewer than 2^21 arcs, or of fewer
+                                   than 2^19 with FIXED pull rounds and a delta; at most 8; pass the
+                                   same opts to llp_workspace_bytes);
                                    stable marriage: proposals per thread per launch; batch: instances per
                                    queue claim; jobs readiness: widest level, in arcs, run by one
                                    workgroup in LDS (default and most 1024; -1 = none) */

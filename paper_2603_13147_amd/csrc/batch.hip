@@ -246,10 +246,10 @@ static int batch_plan(int32_t count, const llp_instance* desc, const llp_opts& o
             if (chunk <= 0) chunk = tc;
         }
     }
-    // 512 threads is the autotuner's usual choice on a large batch (1001 us
-    // against 1372 with 1024 on 8192 instances); with at most two instances per
+    // 512 threads is the autotuner's usual choice on a large batch (984 us
+    // against 1374 with 1024 on 8192 instances); with at most two instances per
     // CU the longest ones set the time, and 1024 threads solve each sooner
-    // (500 instances: 180 us against 247)
+    // (500 instances: 178 us against 237)
     if (block <= 0) block = count <= 2 * device_info().cus ? 1024 : 512;
     if (chunk <= 0) chunk = 1;
     if (block % 64 != 0 || block > 1024) return fail(LLP_E_ARG, "block must be a multiple of 64 up to 1024");

@@ -1721,14 +1721,14 @@ __global__ void k_graph_decode(int* G, int n) {
 // --------------------------------------------------------------- small graphs
 // A graph whose state and row offsets fit in one CU's LDS, solved by one
 // workgroup in one launch (sssp_wg.h): its rounds are separated by a workgroup
-// barrier (about 2 us each) instead of a launch (10 to 19 us each over 512 list
-// segments).  One CU pushes about 0.8 G arcs a second, so the number of arcs
-// sets the limit, and a lower one for few vertices, whose search the grid-wide
-// rounds end in three or four.  Uniform graphs, SSSP, in us here and by
-// grid-wide rounds: 8 arcs per vertex n = 64 36 / 120, n = 4096 118 / 320, 1000 arcs
-// per vertex n = 64 77 / 89; at the limits n = 64, 48 K arcs 67 / 96, n = 256, 62 K
-// 112 / 120, n = 512, 75 K 133 / 180, n = 960, 93 K 186 / 204, n = 4096, 98 K 204 / 252;
-// past them n = 64, 80 K 133 / 99, n = 256, 80 K 339 / 120, n = 512, 100 K 156 / 147,
+// barrier (about 2 us each) instead of a launch (10 to 19 us each).  One CU
+// pushes about 0.8 G arcs a second, so the number of arcs sets the limit, and a
+// lower one for few vertices, whose search the grid-wide rounds end in three or
+// four.  Uniform graphs, SSSP, in us here and by grid-wide rounds: 8 arcs per
+// vertex n = 64 36 / 120, n = 4096 118 / 320, 1000 arcs per vertex n = 64 77 / 89;
+// at the limits n = 64, 48 K arcs 67 / 96, n = 256, 62 K 112 / 120, n = 512,
+// 75 K 133 / 180, n = 960, 93 K 186 / 204, n = 4096, 98 K 204 / 252; past them
+// n = 64, 80 K 133 / 99, n = 256, 80 K 339 / 120, n = 512, 100 K 156 / 147,
 // n = 1250, 120 K 191 / 191.  R-MAT graphs of 70 K arcs, scale 12 144 / 179.
 constexpr int SMALL_N = 16384;     // 142 KB of LDS
 constexpr int SMALL_M = 100000;
